@@ -329,7 +329,7 @@ int bc_read_brick(bc_ctx* ctx, int b, void* dst, size_t cap, int32_t padded_dims
  *
  * bc_cnn_plan: workspace bytes for up to max_n images of max_h x max_w coarse
  *   pixels (parameters, Adam moments, packed BF16 weights, activations,
- *   per-tile partial sums).  BC_E_ARG outside 1 <= max_n <= 64, sizes in
+ *   partial sums).  BC_E_ARG outside 1 <= max_n <= 64, sizes in
  *   [1, 8192]; BC_E_STATE once bound.
  * bc_cnn_bind: caller-allocated device workspace (256-byte aligned), kept alive
  *   by the caller; BC_E_NOMEM if smaller than planned.

@@ -411,15 +411,19 @@ struct CnnLayout {
   size_t w, m, v, g;                 // FP32 parameter vectors
   size_t f1, f2, f3, b3, b2;         // packed fragments: forward 1..3, backward-data 3 and 2
   size_t a1, a2, gy, gz2, gz1;       // BF16 NHWC activations / gradients
-  size_t part, loss;                 // per-tile partial sums
+  size_t part, loss;                 // partial sums: weight gradients per workgroup, squared error per tile
   size_t coarse, val;                // learned frames: coarse render, validation tiles
   size_t total;
   int64_t tiles;
+  int n_part;                        // workgroups of a backward-weights launch
 };
 
 // fragment bytes: ks * nt * 64 lanes * 8 BF16
 constexpr size_t frag_bytes(int ks, int nt) { return (size_t)ks * nt * 64 * 8 * 2; }
-constexpr int kPartWidth = 32 * 288 + 32;   // widest per-tile partial (layer 2)
+// Workgroups of a backward-weights launch, at most: two or three to a compute
+// unit fill the chip, and every further one is another partial vector of all
+// parameters (60 KB) to be written and summed.
+constexpr int64_t kMaxParts = 768;
 
 CnnLayout cnn_layout(int n, int h, int w) {
   CnnLayout L;
@@ -441,7 +445,10 @@ CnnLayout cnn_layout(int n, int h, int w) {
   L.gz2 = take(px * 32 * 2);
   L.gz1 = take(px * 32 * 2);
   L.tiles = (int64_t)n * ((h + 15) / 16) * ((w + 15) / 16);
-  L.part = take((size_t)L.tiles * kPartWidth * 4);
+  // whole rounds of tiles: every workgroup has the same number, or one less
+  const int64_t rounds = (L.tiles + kMaxParts - 1) / kMaxParts;
+  L.n_part = (int)((L.tiles + rounds - 1) / rounds);
+  L.part = take((size_t)std::min(L.tiles, kMaxParts) * CNN_N_PARAMS * 4);
   L.loss = take((size_t)L.tiles * 4);
   L.coarse = take(px * 16);
   L.val = take(px * 4 * 16);
@@ -1439,8 +1446,9 @@ int cnn_check_images(bc_ctx* c, const char* who, int n, int h, int w) {
   return BC_OK;
 }
 
-// forward + loss + backward into the gradient vector (no update)
-int cnn_gradients(bc_ctx* c, const float* coarse, const float* target, int n, int h, int w, hipStream_t st) {
+// forward + loss + backward into the gradient vector, and the update `u` if it has one
+int cnn_gradients(bc_ctx* c, const float* coarse, const float* target, int n, int h, int w, const CnnUpdate& u,
+                  hipStream_t st) {
   const CnnLayout L = cnn_layout(n, h, w);
   char* ws = c->cnn_ws;
   auto U16 = [&](size_t off) { return reinterpret_cast<uint16_t*>(ws + off); };
@@ -1465,19 +1473,18 @@ int cnn_gradients(bc_ctx* c, const float* coarse, const float* target, int n, in
   HIPCHECK(c, cnn_launch_layer(3, 1, bd, n, st));
   bd.in = U16(L.gz2); bd.out = U16(L.gz1); bd.mask = U16(L.a1); bd.wf = FR(L.b2);
   HIPCHECK(c, cnn_launch_layer(2, 1, bd, n, st));
-  // backward-weights per layer, then deterministic reductions
-  float* g = F32(L.g);
-  struct { int layer, cin, cout; const float* img; const uint16_t* x; const uint16_t* gr; int w_off, b_off; } jobs[3] = {
-      {3, 32, 16, nullptr, U16(L.a2), U16(L.gy), CNN_OFF_W3, CNN_OFF_B3},
-      {2, 32, 32, nullptr, U16(L.a1), U16(L.gz2), CNN_OFF_W2, CNN_OFF_B2},
-      {1, 4, 32, coarse, nullptr, U16(L.gz1), CNN_OFF_W1, CNN_OFF_B1}};
+  // backward-weights per layer, then one deterministic reduction
+  struct { int layer; const float* img; const uint16_t* x; const uint16_t* gr; int off; } jobs[3] = {
+      {3, nullptr, U16(L.a2), U16(L.gy), CNN_OFF_W3},
+      {2, nullptr, U16(L.a1), U16(L.gz2), CNN_OFF_W2},
+      {1, coarse, nullptr, U16(L.gz1), CNN_OFF_W1}};
   for (auto& j : jobs) {
     CnnWgradArgs wa{};
-    wa.img = j.img; wa.x = j.x; wa.g = j.gr; wa.part = F32(L.part); wa.h = h; wa.w = w;
-    HIPCHECK(c, cnn_launch_wgrad(j.layer, wa, n, st));
-    const int nw = j.cout * j.cin * 9;
-    HIPCHECK(c, cnn_launch_reduce(F32(L.part), L.tiles, nw + j.cout, g + j.w_off, g + j.b_off, nw, st));
+    wa.img = j.img; wa.x = j.x; wa.g = j.gr; wa.part = F32(L.part); wa.off = j.off; wa.n_tiles = (int32_t)L.tiles;
+    wa.h = h; wa.w = w;
+    HIPCHECK(c, cnn_launch_wgrad(j.layer, wa, L.n_part, st));
   }
+  HIPCHECK(c, cnn_launch_reduce(F32(L.part), L.n_part, F32(L.g), u, cnn_pack_table(c, L), st));
   return BC_OK;
 }
 
@@ -1609,7 +1616,7 @@ int bc_cnn_gradients(bc_ctx* c, const float* coarse, const float* target, int n,
   if (r) return r;
   HIPCHECK(c, hipSetDevice(c->device));
   // the per-layer buffers are laid out for the size of this call
-  r = cnn_gradients(c, coarse, target, n, h, w, nullptr);
+  r = cnn_gradients(c, coarse, target, n, h, w, CnnUpdate{}, nullptr);
   if (r) return r;
   const CnnLayout L = cnn_layout(n, h, w);
   if (grad) HIPCHECK(c, hipMemcpy(grad, c->cnn_ws + L.g, sizeof(float) * CNN_N_PARAMS, hipMemcpyDeviceToHost));
@@ -1628,15 +1635,13 @@ int bc_cnn_train_step(bc_ctx* c, const float* coarse, const float* target, int n
   if (r) return r;
   HIPCHECK(c, hipSetDevice(c->device));
   hipStream_t st = static_cast<hipStream_t>(stream);
-  r = cnn_gradients(c, coarse, target, n, h, w, st);
-  if (r) return r;
-  const CnnLayout Lg = cnn_layout(n, h, w);
   const CnnLayout L = cnn_layout(c->cnn_max_n, c->cnn_max_h, c->cnn_max_w);
-  float* wv = reinterpret_cast<float*>(c->cnn_ws + L.w);
+  r = cnn_gradients(c, coarse, target, n, h, w,
+                    cnn_adam(reinterpret_cast<float*>(c->cnn_ws + L.w), reinterpret_cast<float*>(c->cnn_ws + L.m),
+                             reinterpret_cast<float*>(c->cnn_ws + L.v), lr, c->cnn_step + 1),
+                    st);
+  if (r) return r;
   c->cnn_step += 1;
-  HIPCHECK(c, cnn_launch_adam(wv, reinterpret_cast<float*>(c->cnn_ws + L.m), reinterpret_cast<float*>(c->cnn_ws + L.v),
-                              reinterpret_cast<const float*>(c->cnn_ws + Lg.g), CNN_N_PARAMS, lr, c->cnn_step, st));
-  HIPCHECK(c, cnn_launch_pack(wv, cnn_pack_table(c, L), st));
   if (loss) return cnn_read_loss(c, n, h, w, loss, st);
   return BC_OK;
 }

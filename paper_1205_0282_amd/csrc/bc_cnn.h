@@ -39,8 +39,17 @@ struct CnnWgradArgs {
   const float* img;        // FP32 coarse images when the layer input is the image
   const uint16_t* x;       // BF16 NHWC layer input otherwise
   const uint16_t* g;       // BF16 NHWC gradient of the layer output
-  float* part;             // per-tile partial sums: [tile][cout*9*cin + cout]
+  float* part;             // partial sums: [workgroup][CNN_N_PARAMS], this layer's at off
+  int32_t off;
+  int32_t n_tiles;         // 16x16 tiles of all images
   int32_t h, w;
+};
+
+// Adam step of the flat parameters (w = nullptr: none)
+struct CnnUpdate {
+  float *w, *m, *v;
+  float lr, b1, b2, eps;
+  float c1, c2;            // bias corrections 1 - b1^step, 1 - b2^step
 };
 
 struct CnnPackEntry {
@@ -54,9 +63,9 @@ struct CnnPackTable {
 
 hipError_t cnn_launch_infer(const CnnInferArgs& a, int n, hipStream_t st);
 hipError_t cnn_launch_layer(int layer, int mode, const CnnLayerArgs& a, int n, hipStream_t st);
-hipError_t cnn_launch_wgrad(int layer, const CnnWgradArgs& a, int n, hipStream_t st);
-hipError_t cnn_launch_reduce(const float* part, int64_t n_tiles, int width, float* grad_w, float* grad_b, int n_w,
+hipError_t cnn_launch_wgrad(int layer, const CnnWgradArgs& a, int n_workgroups, hipStream_t st);
+// gradient = sum of n_part partial vectors; with u.w also the Adam step and the packed fragments
+hipError_t cnn_launch_reduce(const float* part, int n_part, float* grad, const CnnUpdate& u, const CnnPackTable& tab,
                              hipStream_t st);
-hipError_t cnn_launch_adam(float* w, float* m, float* v, const float* g, int n, float lr, int64_t step,
-                           hipStream_t st);
+CnnUpdate cnn_adam(float* w, float* m, float* v, float lr, int64_t step);
 hipError_t cnn_launch_pack(const float* w, const CnnPackTable& tab, hipStream_t st);

@@ -16,8 +16,8 @@
 // LDS-resident activations), per-layer training forward with the loss in the
 // last layer's epilogue, backward-data (a forward convolution with flipped,
 // channel-transposed weights and the ReLU mask in the epilogue),
-// backward-weights (GEMM over the pixels of a tile, partial sums per tile,
-// then a deterministic reduction), Adam, and the weight packer.
+// backward-weights (GEMM over the pixels, partial sums per workgroup), their
+// deterministic reduction with the Adam step, and the weight packer.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "bc_cnn.h"
@@ -354,90 +354,203 @@ __global__ __launch_bounds__(256) void layer_kernel(CnnLayerArgs a) {
 }
 
 // ------------------------------------------------------------------ backward-weights
-// Per 16x16 tile: dW[o][c][tap] += sum_p g[p][o] x[p + tap][c] as a GEMM with
-// rows o (COUT), columns n = tap*CIN + c, reduction over the tile's 256 pixels;
-// db[o] += sum_p g[p][o].  Partial sums per tile go to `part`.
+// dW[o][c][tap] = sum_p g[p][o] x[p + tap][c] and db[o] = sum_p g[p][o], as a
+// GEMM with rows o, columns (tap, c) and the reduction over pixels, 32 to a
+// matrix instruction (two rows of a 16x16 tile).  Both operands need eight
+// consecutive pixels of one channel per lane, so a tile is staged in LDS
+// channel by channel (pixels contiguous): operand A is then one 16-byte read,
+// and one 20-byte read of a row of x gives operand B of the row's three taps
+// (the tap one to the right is the same bytes shifted by one pixel).  A
+// workgroup keeps its sums in the accumulators over all its tiles
+// (blockIdx.x, + gridDim.x, ...) and writes one partial vector at its end, in
+// the layout of the parameters.  At 960x540 the three launches take 34, 45 and
+// 25 us and the reduction of all layers with the update 11 us; one partial
+// vector per tile, gathered element by element from LDS, took 46, 85 and 37
+// us, and 473 us for each layer's reduction (one thread per parameter).
+constexpr int XROW = 24;               // elements per staged row of x: 18 pixels, rows 16-byte aligned
+constexpr int XCH = 18 * XROW + 8;     // elements per staged channel of x and of g: the 16 channels that
+constexpr int GCH = 256 + 8;           // a read touches start 4 banks apart, so their 16 bytes cover all banks once
+
+// the 16-bit elements j of eight channels of two neighbouring pixels, as one
+// pair (a in the low half) per channel at d[j * stride] (in pairs)
+__device__ __forceinline__ void store_pairs(uint32_t* d, int stride, uint4 a, uint4 b) {
+  const uint32_t av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    d[(2 * j) * stride] = __builtin_amdgcn_perm(bv[j], av[j], 0x05040100u);
+    d[(2 * j + 1) * stride] = __builtin_amdgcn_perm(bv[j], av[j], 0x07060302u);
+  }
+}
+
 template <int CIN, int COUT>
 __global__ __launch_bounds__(256) void wgrad_kernel(CnnWgradArgs a) {
-  constexpr int SIN = CIN == 4 ? 4 : PSTRIDE;
   constexpr int NCOL = 9 * CIN;
-  constexpr int NTN = (NCOL + 15) / 16;
-  __shared__ __attribute__((aligned(16))) uint16_t xt[18 * 18 * SIN];
-  __shared__ __attribute__((aligned(16))) uint16_t gt[256 * COUT];
+  constexpr bool IMG = CIN == 4;
+  // the four waves share the work as (o tile) x (c tile) x (half of the rows)
+  constexpr int OT = COUT / 16, CT = IMG ? 1 : CIN / 16, KH = 4 / (OT * CT);
+  constexpr int NB = IMG ? 3 : 9;      // accumulators: taps, or rows of taps (columns 4 dx + c) of the image
+  __shared__ __attribute__((aligned(16))) uint16_t xt[CIN * XCH];
+  __shared__ __attribute__((aligned(16))) uint16_t gt[COUT * GCH];
   const int H = a.h, W = a.w;
-  const int n = blockIdx.z;
-  const int oy = blockIdx.y * 16, ox = blockIdx.x * 16;
   const int64_t plane = (int64_t)H * W;
-  const int64_t tile = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-  stage_tile<CIN>(xt, SIN, a.img ? a.img + n * plane * 4 : nullptr, a.x ? a.x + n * plane * CIN : nullptr, H, W, oy, ox);
-  for (int i = threadIdx.x; i < 256; i += blockDim.x) {
-    const int gy = oy + i / 16, gx = ox + i % 16;
-    const bool in = gy < H && gx < W;
-    const uint4* src = reinterpret_cast<const uint4*>(a.g + (n * plane + (int64_t)gy * W + gx) * COUT);
-    for (int q = 0; q < COUT / 8; ++q)
-      *reinterpret_cast<uint4*>(gt + i * COUT + 8 * q) = in ? src[q] : make_uint4(0, 0, 0, 0);
-  }
-  __syncthreads();
-  float* part = a.part + tile * (int64_t)(COUT * NCOL + COUT);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+  const int tx = (W + 15) >> 4, ty = (H + 15) >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = (int)__builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, r = lane & 15;
-  for (int job = wave; job < (COUT / 16) * NTN; job += nwaves) {
-    const int mt = job / NTN, nt = job % NTN;
-    const int o = mt * 16 + r;
-    const int col = nt * 16 + r;
-    const bool cval = col < NCOL;
-    const int tap = cval ? col / CIN : 0, c = cval ? col % CIN : 0;
-    const int dy = tap / 3, dx = tap % 3;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int ks = 0; ks < 8; ++ks) {
-      uint16_t av[8], bv[8];
-      for (int i = 0; i < 8; ++i) {
-        const int p = ks * 32 + 8 * g + i;
-        av[i] = gt[p * COUT + o];
-        bv[i] = cval ? xt[((p / 16 + dy) * 18 + (p % 16) + dx) * SIN + c] : (uint16_t)0;
+  const int ot = wave % OT, ct = (wave / OT) % CT, kh = wave / (OT * CT);
+  f32x4 acc[NB], accb = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < NB; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bf16x8 ones = as_bf16x8(make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
+  for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
+    const int n = tile / (tx * ty), rem = tile - n * (tx * ty);
+    const int oy = (rem / tx) * 16, ox = (rem % tx) * 16;
+    __syncthreads();   // the tile before has been read
+    uint32_t* xp = reinterpret_cast<uint32_t*>(xt);
+    uint32_t* gp = reinterpret_cast<uint32_t*>(gt);
+    // x: 18 rows of nine pixel pairs, zero outside the image
+    constexpr int XQ = IMG ? 1 : CIN / 8;
+    for (int i = tid; i < 162 * XQ; i += 256) {
+      const int q = i % XQ, pr = i / XQ, row = pr / 9, k = pr % 9;
+      const int gy = oy - 1 + row, gx = ox - 1 + 2 * k;
+      const bool in0 = gy >= 0 && gy < H && gx >= 0 && gx < W, in1 = gy >= 0 && gy < H && gx + 1 >= 0 && gx + 1 < W;
+      const int64_t pix = n * plane + (int64_t)gy * W + gx;
+      uint32_t* d = xp + (8 * q) * (XCH / 2) + row * (XROW / 2) + k;
+      if constexpr (IMG) {
+        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 u = in0 ? reinterpret_cast<const float4*>(a.img)[pix] : z;
+        const float4 v = in1 ? reinterpret_cast<const float4*>(a.img)[pix + 1] : z;
+        d[0] = bf16_bits(u.x) | (uint32_t)bf16_bits(v.x) << 16;
+        d[XCH / 2] = bf16_bits(u.y) | (uint32_t)bf16_bits(v.y) << 16;
+        d[XCH] = bf16_bits(u.z) | (uint32_t)bf16_bits(v.z) << 16;
+        d[3 * (XCH / 2)] = bf16_bits(u.w) | (uint32_t)bf16_bits(v.w) << 16;
+      } else {
+        const uint4 z = make_uint4(0, 0, 0, 0);
+        const uint4 u = in0 ? reinterpret_cast<const uint4*>(a.x + pix * CIN)[q] : z;
+        const uint4 v = in1 ? reinterpret_cast<const uint4*>(a.x + (pix + 1) * CIN)[q] : z;
+        store_pairs(d, XCH / 2, u, v);
       }
-      const uint4 ua = make_uint4(av[0] | (uint32_t)av[1] << 16, av[2] | (uint32_t)av[3] << 16,
-                                  av[4] | (uint32_t)av[5] << 16, av[6] | (uint32_t)av[7] << 16);
-      const uint4 ub = make_uint4(bv[0] | (uint32_t)bv[1] << 16, bv[2] | (uint32_t)bv[3] << 16,
-                                  bv[4] | (uint32_t)bv[5] << 16, bv[6] | (uint32_t)bv[7] << 16);
-      acc = mfma(as_bf16x8(ua), as_bf16x8(ub), acc);
     }
-    if (cval)
-      for (int i = 0; i < 4; ++i) {
-        const int oo = mt * 16 + 4 * g + i;
-        part[oo * NCOL + c * 9 + tap] = acc[i];   // layout W[o][c][dy][dx]
+    constexpr int GQ = COUT / 8;
+    for (int i = tid; i < 128 * GQ; i += 256) {
+      const int q = i % GQ, pr = i / GQ, row = pr >> 3, k = pr & 7;
+      const int gy = oy + row, gx = ox + 2 * k;
+      const int64_t pix = n * plane + (int64_t)gy * W + gx;
+      const uint4 z = make_uint4(0, 0, 0, 0);
+      const uint4 u = gy < H && gx < W ? reinterpret_cast<const uint4*>(a.g + pix * COUT)[q] : z;
+      const uint4 v = gy < H && gx + 1 < W ? reinterpret_cast<const uint4*>(a.g + (pix + 1) * COUT)[q] : z;
+      store_pairs(gp + (8 * q) * (GCH / 2) + pr, GCH / 2, u, v);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 8 / KH; ++s) {
+      const int row = 2 * (s + (8 / KH) * kh) + (g >> 1), xo = 8 * (g & 1);
+      const bf16x8 av = as_bf16x8(*reinterpret_cast<const uint4*>(gt + (ot * 16 + r) * GCH + row * 16 + xo));
+      if (ct == 0) accb = mfma(av, ones, accb);
+#pragma unroll
+      for (int dy = 0; dy < 3; ++dy) {
+        // pixels xo .. xo + 9 of the row dy of the lane's channel
+        const uint16_t* src = xt + (IMG ? (r & 3) : ct * 16 + r) * XCH + (row + dy) * XROW + xo;
+        const uint4 lo = *reinterpret_cast<const uint4*>(src);
+        const uint32_t hi = *reinterpret_cast<const uint32_t*>(src + 8);
+        if constexpr (IMG) {
+          // columns 4 dx + c: the lane's dx = r / 4 (columns 12-15 are not used)
+          const int sh = 16 * min(r >> 2, 2);
+          auto pick = [&](uint32_t p, uint32_t q) { return (uint32_t)((((uint64_t)q << 32) | p) >> sh); };
+          acc[dy] = mfma(av, as_bf16x8(make_uint4(pick(lo.x, lo.y), pick(lo.y, lo.z), pick(lo.z, lo.w), pick(lo.w, hi))),
+                         acc[dy]);
+        } else {
+          auto mid = [&](uint32_t p, uint32_t q) { return __builtin_amdgcn_alignbit(q, p, 16); };
+          acc[3 * dy] = mfma(av, as_bf16x8(lo), acc[3 * dy]);
+          acc[3 * dy + 1] = mfma(
+              av, as_bf16x8(make_uint4(mid(lo.x, lo.y), mid(lo.y, lo.z), mid(lo.z, lo.w), mid(lo.w, hi))), acc[3 * dy + 1]);
+          acc[3 * dy + 2] = mfma(av, as_bf16x8(make_uint4(lo.y, lo.z, lo.w, hi)), acc[3 * dy + 2]);
+        }
       }
+    }
   }
-  if ((int)threadIdx.x < COUT) {
-    float s = 0.0f;
-    for (int p = 0; p < 256; ++p) s += bf16_float(gt[p * COUT + threadIdx.x]);
-    part[COUT * NCOL + threadIdx.x] = s;
+  if constexpr (KH == 2) {
+    // the two halves of the rows meet in LDS
+    float* mine = reinterpret_cast<float*>(IMG ? gt : xt) + ((wave & 1) * 64 + lane) * 4;
+    static_assert((IMG ? sizeof(gt) : sizeof(xt)) >= 512 * (NB + 1) * sizeof(float), "accumulators fit");
+    __syncthreads();
+    if (kh == 1) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mine[j * 512 + i] = acc[j][i];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) mine[NB * 512 + i] = accb[i];
+    }
+    __syncthreads();
+    if (kh == 1) return;
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[j][i] += mine[j * 512 + i];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) accb[i] += mine[NB * 512 + i];
+  }
+  // rows o = 16 ot + 4 g + i, layout W[o][c][dy][dx], then b[o]
+  float* part = a.part + (int64_t)blockIdx.x * CNN_N_PARAMS + a.off;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int o = ot * 16 + 4 * g + i;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      if constexpr (IMG) {
+        if (r < 12) part[o * NCOL + (r & 3) * 9 + 3 * j + (r >> 2)] = acc[j][i];
+      } else {
+        part[o * NCOL + (ct * 16 + r) * 9 + j] = acc[j][i];
+      }
+    }
+    if (ct == 0 && r == 0) part[COUT * NCOL + o] = accb[i];
   }
 }
 
-// sum of the per-tile partials into the flat gradient (fixed order: deterministic)
-__global__ void reduce_kernel(const float* __restrict__ part, int64_t n_tiles, int width, float* __restrict__ grad_w,
-                              float* __restrict__ grad_b, int n_w) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= width) return;
+// ------------------------------------------------------------------ reduction, Adam and packing
+// element of the packed fragments (see pack_kernel) that holds B[k][n]
+__device__ __forceinline__ int frag_index(int k, int n, int nt) {
+  return (((k >> 5) * nt + (n >> 4)) * 64 + 16 * ((k >> 3) & 3) + (n & 15)) * 8 + (k & 7);
+}
+
+// Sums the workgroups' partial vectors into the gradient, 64 parameters per
+// workgroup: wave k adds the vectors k, k + 16, ... and the sixteen sums are
+// added in order (fixed orders: deterministic).  With an update (u.w), the
+// thread that holds a parameter's gradient also takes its Adam step and
+// writes the weight's BF16 value into the fragments that the layers read, in
+// place of two more launches.
+__global__ __launch_bounds__(1024) void reduce_kernel(const float* __restrict__ part, int n_part,
+                                                      float* __restrict__ grad, CnnUpdate u, CnnPackTable tab) {
+  __shared__ float red[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = blockIdx.x * 64 + lane;
   float s = 0.0f;
-  for (int64_t t = 0; t < n_tiles; ++t) s += part[t * width + j];
-  if (j < n_w) grad_w[j] = s;
-  else grad_b[j - n_w] = s;
-}
-
-// ------------------------------------------------------------------ Adam and packing
-__global__ void adam_kernel(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
-                            const float* __restrict__ g, int n, float lr, float b1, float b2, float eps, float c1,
-                            float c2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.0f - b1) * gi;
-  const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  w[i] = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  if (j < CNN_N_PARAMS) {
+#pragma unroll 8
+    for (int t = wave; t < n_part; t += 16) s += part[(int64_t)t * CNN_N_PARAMS + j];
+  }
+  red[wave][lane] = s;
+  __syncthreads();
+  if (wave != 0 || j >= CNN_N_PARAMS) return;
+  float gi = red[0][lane];
+#pragma unroll
+  for (int k = 1; k < 16; ++k) gi += red[k][lane];
+  grad[j] = gi;
+  if (!u.w) return;
+  const float mi = u.b1 * u.m[j] + (1.0f - u.b1) * gi;
+  const float vi = u.b2 * u.v[j] + (1.0f - u.b2) * gi * gi;
+  u.m[j] = mi;
+  u.v[j] = vi;
+  const float w = u.w[j] - u.lr * (mi / u.c1) / (sqrtf(vi / u.c2) + u.eps);
+  u.w[j] = w;
+  const uint16_t h = bf16_bits(w);
+  for (int e = 0; e < tab.n; ++e) {
+    const CnnPackEntry& p = tab.e[e];
+    const int x = j - p.w_off;
+    if (x < 0 || x >= p.cout * p.cin * 9) continue;   // another layer's weight, or a bias
+    const int o = x / (9 * p.cin), c = (x / 9) % p.cin, tap = x % 9;
+    p.dst[p.transposed ? frag_index((8 - tap) * p.cout + o, c, p.nt) : frag_index(tap * p.cin + c, o, p.nt)] = h;
+  }
 }
 
 // B fragments: element i of lane l of (ks, nt) is B[k][n] with
@@ -496,27 +609,33 @@ hipError_t cnn_launch_layer(int layer, int mode, const CnnLayerArgs& a, int n, h
   return hipGetLastError();
 }
 
-hipError_t cnn_launch_wgrad(int layer, const CnnWgradArgs& a, int n, hipStream_t st) {
-  dim3 grid((a.w + 15) / 16, (a.h + 15) / 16, n);
-  if (layer == 1) wgrad_kernel<4, 32><<<grid, 256, 0, st>>>(a);
-  else if (layer == 2) wgrad_kernel<32, 32><<<grid, 256, 0, st>>>(a);
-  else if (layer == 3) wgrad_kernel<32, 16><<<grid, 256, 0, st>>>(a);
+hipError_t cnn_launch_wgrad(int layer, const CnnWgradArgs& a, int n_workgroups, hipStream_t st) {
+  if (layer == 1) wgrad_kernel<4, 32><<<n_workgroups, 256, 0, st>>>(a);
+  else if (layer == 2) wgrad_kernel<32, 32><<<n_workgroups, 256, 0, st>>>(a);
+  else if (layer == 3) wgrad_kernel<32, 16><<<n_workgroups, 256, 0, st>>>(a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t cnn_launch_reduce(const float* part, int64_t n_tiles, int width, float* grad_w, float* grad_b, int n_w,
+hipError_t cnn_launch_reduce(const float* part, int n_part, float* grad, const CnnUpdate& u, const CnnPackTable& tab,
                              hipStream_t st) {
-  reduce_kernel<<<(width + 255) / 256, 256, 0, st>>>(part, n_tiles, width, grad_w, grad_b, n_w);
+  reduce_kernel<<<(CNN_N_PARAMS + 63) / 64, 1024, 0, st>>>(part, n_part, grad, u, tab);
   return hipGetLastError();
 }
 
-hipError_t cnn_launch_adam(float* w, float* m, float* v, const float* g, int n, float lr, int64_t step,
-                           hipStream_t st) {
+CnnUpdate cnn_adam(float* w, float* m, float* v, float lr, int64_t step) {
   const double b1 = 0.9, b2 = 0.999;
-  const float c1 = (float)(1.0 - pow(b1, (double)step)), c2 = (float)(1.0 - pow(b2, (double)step));
-  adam_kernel<<<(n + 255) / 256, 256, 0, st>>>(w, m, v, g, n, lr, (float)b1, (float)b2, 1e-8f, c1, c2);
-  return hipGetLastError();
+  CnnUpdate u;
+  u.w = w;
+  u.m = m;
+  u.v = v;
+  u.lr = lr;
+  u.b1 = (float)b1;
+  u.b2 = (float)b2;
+  u.eps = 1e-8f;
+  u.c1 = (float)(1.0 - pow(b1, (double)step));
+  u.c2 = (float)(1.0 - pow(b2, (double)step));
+  return u;
 }
 
 hipError_t cnn_launch_pack(const float* w, const CnnPackTable& tab, hipStream_t st) {

@@ -136,3 +136,28 @@ def test_training_reduces_loss(caster):
     for _ in range(60):
         last = caster.cnn_train_step(xd, td, lr=2e-3)
     assert last < 0.7 * first, (first, last)
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 17, 33), (13, 1, 960)])
+def test_weight_gradients_over_tiles(shape):
+    """The partial sums of the weight gradients: less than one tile, ragged
+    tiles of several images, and more tiles than workgroups (780 in two
+    rounds).  Per parameter block, 1e-3 as above: the sums are FP32 either
+    way, and a block's error comes from the rare BF16 rounding flip."""
+    import torch
+    n, h, w = shape
+    bc = binding.BrickCaster(0)
+    bc.cnn_setup(n, h, w)
+    p = _params(12)
+    bc.cnn_set_weights(p)
+    x, t = _images(np.random.default_rng(13), n, h, w)
+    if w == 1:
+        x += np.float32(0.25)                      # (a single pixel lies in no background)
+    g_gpu, _ = bc.cnn_gradients(torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda())
+    bc.close()
+    g_ref = np.zeros(cnn.N_PARAMS)
+    for i in range(n):
+        out, cache = cnn.forward(p.astype(np.float64), x[i], bf16=True)
+        g_ref += cnn.backward(cache, out, t[i], bf16=True, count=n * out.size)
+    for lo, hi in [(0, 1152), (1152, 1184), (1184, 10400), (10400, 10432), (10432, 15040), (15040, 15056)]:
+        assert _rel(g_gpu[lo:hi], g_ref[lo:hi]) <= 1e-3, (lo, hi, _rel(g_gpu[lo:hi], g_ref[lo:hi]))
