@@ -96,7 +96,7 @@ struct bc_ctx {
   // another (the validation pass of a learned frame)
   size_t off_views_b = 0, off_order_b = 0, off_rects_b = 0, off_item_base_b = 0, off_item_perm_b = 0,
          off_item_entry_b = 0, off_ctr_b = 0;
-  int max_occ_words = 0;
+  int max_occ_w[3] = {0, 0, 0};   // most occupancy words of a brick per axis
   void* dev[4] = {nullptr, nullptr, nullptr, nullptr};
   // per-frame input ring (pinned host memory, kPasses pass inputs per slot) and events
   BcFrameIn* pinned[2] = {nullptr, nullptr};
@@ -593,7 +593,8 @@ int bc_plan(bc_ctx* c, const bc_volume_desc* d, int max_views, int max_w, int ma
   c->elem_bytes = d->storage == BC_F32 ? 4 : (d->storage == BC_F16 ? 2 : 1);
   c->src_elem_bytes = d->src_dtype == BC_F32 ? 4 : 2;
   c->bricks.assign(c->n_bricks, BcBrick{});
-  int64_t off = 0, occ_words = 0, max_words = 0;
+  for (int& w : c->max_occ_w) w = 0;
+  int64_t off = 0, occ_words = 0;
   size_t max_region = 0;
   for (int bz = 0; bz < nb[2]; ++bz)
     for (int by = 0; by < nb[1]; ++by)
@@ -619,7 +620,7 @@ int bc_plan(bc_ctx* c, const bc_volume_desc* d, int max_views, int max_w, int ma
         b.occ_offset = occ_words;
         const int64_t words = (int64_t)b.occ_w[0] * b.occ_w[1] * b.occ_w[2];
         occ_words += words;
-        max_words = std::max<int64_t>(max_words, words);
+        for (int a = 0; a < 3; ++a) c->max_occ_w[a] = std::max(c->max_occ_w[a], (int)b.occ_w[a]);
         max_region = std::max(max_region, (size_t)region);
       }
   // screen tiles of a frame, for the largest count over the tile shapes
@@ -656,7 +657,6 @@ int bc_plan(bc_ctx* c, const bc_volume_desc* d, int max_views, int max_w, int ma
   c->off_ctr_b = m; m = align256(m + sizeof(BcCounters));
   c->off_occ = m; m = align256(m + sizeof(uint32_t) * (size_t)occ_words);
   c->bytes[1] = m;
-  c->max_occ_words = (int)max_words;
   c->bytes[2] = align256((size_t)max_tiles * 64 * 16);
   c->bytes[3] = align256(max_region * c->src_elem_bytes);
   for (int i = 0; i < 4; ++i) bytes_out[i] = c->bytes[i];
@@ -969,7 +969,7 @@ int render_impl(bc_ctx* c, float* out, void* stream, float4* sub, int64_t sub_ca
   f.fin_bytes = (int32_t)fin_bytes;
   if (classify) {
     HIPCHECK(c, hipMemcpyAsync(meta + c->off_fin, pins, fin_bytes, hipMemcpyHostToDevice, st));
-    HIPCHECK(c, bc_launch_classify(f, c->max_occ_words, st));
+    HIPCHECK(c, bc_launch_classify(f, c->max_occ_w, st));
   }
   // the frame: the kernels of every pass (each pass's set-up kernel first
   // copies the pass inputs from the pinned slot)

@@ -60,7 +60,8 @@ struct BcFramePtrs {
 };
 
 hipError_t bc_launch_setup(const BcFramePtrs& f, hipStream_t st);
-hipError_t bc_launch_classify(const BcFramePtrs& f, int max_words, hipStream_t st);
+// max_w bounds the bricks' occupancy words per axis
+hipError_t bc_launch_classify(const BcFramePtrs& f, const int max_w[3], hipStream_t st);
 hipError_t bc_launch_render(const BcFramePtrs& f, int n_workgroups, hipStream_t st);
 hipError_t bc_launch_composite(const BcFramePtrs& f, float4* out, hipStream_t st);
 hipError_t bc_launch_psnr(const BcFramePtrs& f, const float4* ref, const float4* img, hipStream_t st);
