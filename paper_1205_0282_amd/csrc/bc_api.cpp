@@ -721,12 +721,24 @@ int bc_load_bricks(bc_ctx* c, const void* src, const int64_t strides[3], int src
   HIPCHECK(c, bc_launch_init_minmax(ctr, c->n_bricks, st));
   // launch bounds: the largest brick's ghosted rows (y * z) and rows of
   // micro-blocks along x (y * z in micro-blocks)
-  int max_rows = 0;
+  int max_rows = 0, max_mb0 = 0;
   int64_t max_mb_rows = 0;
   for (const BcBrick& hb : c->bricks) {
     max_rows = std::max(max_rows, (hb.hi[1] - hb.lo[1] + 2) * (hb.hi[2] - hb.lo[2] + 2));
     max_mb_rows = std::max<int64_t>(max_mb_rows, (int64_t)hb.mb[1] * hb.mb[2]);
+    max_mb0 = std::max(max_mb0, (int)hb.mb[0]);
   }
+  // FP8 codes need the brick's range first; the other forms' encode takes it on the way
+  auto convert = [&](const BcLoadSrc& s, int first, int count) -> hipError_t {
+    hipError_t e = hipSuccess;
+    if (d.storage == BC_FP8_E4M3) {
+      e = bc_launch_minmax(s, dbricks, first, count, max_rows, ctr, st);
+      if (e == hipSuccess) e = bc_launch_finalize(dbricks, ctr, first, count, d.storage, st);
+    }
+    if (e == hipSuccess) e = bc_launch_encode(s, dbricks, first, count, max_mb_rows, max_mb0, d.storage, c->dev[0], ctr, st);
+    if (e == hipSuccess && d.storage != BC_FP8_E4M3) e = bc_launch_finalize(dbricks, ctr, first, count, d.storage, st);
+    return e;
+  };
   if (src_on_device) {
     // the whole share is on the device: every brick in one launch per step
     BcLoadSrc s;
@@ -737,9 +749,7 @@ int bc_load_bricks(bc_ctx* c, const void* src, const int64_t strides[3], int src
       s.strides[a] = strides[a];
       s.origin[a] = (int32_t)box_lo[a];
     }
-    HIPCHECK(c, bc_launch_minmax(s, dbricks, 0, c->n_bricks, max_rows, ctr, st));
-    HIPCHECK(c, bc_launch_finalize(dbricks, ctr, 0, c->n_bricks, d.storage, st));
-    HIPCHECK(c, bc_launch_encode(s, dbricks, 0, c->n_bricks, max_mb_rows, d.storage, c->dev[0], st));
+    HIPCHECK(c, convert(s, 0, c->n_bricks));
   }
   // a host source goes through the load scratch region one brick at a time
   for (int b = 0; b < c->n_bricks && !src_on_device; ++b) {
@@ -785,9 +795,7 @@ int bc_load_bricks(bc_ctx* c, const void* src, const int64_t strides[3], int src
       s.strides[2] = rx * ry;
       for (int a = 0; a < 3; ++a) s.origin[a] = (int32_t)rlo[a];
     }
-    HIPCHECK(c, bc_launch_minmax(s, dbricks, b, 1, max_rows, ctr, st));
-    HIPCHECK(c, bc_launch_finalize(dbricks, ctr, b, 1, d.storage, st));
-    HIPCHECK(c, bc_launch_encode(s, dbricks, b, 1, max_mb_rows, d.storage, c->dev[0], st));
+    HIPCHECK(c, convert(s, b, 1));
     HIPCHECK(c, hipStreamSynchronize(st));
   }
   HIPCHECK(c, hipStreamSynchronize(st));

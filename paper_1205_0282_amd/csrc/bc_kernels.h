@@ -15,13 +15,15 @@ struct BcLoadSrc {
 hipError_t bc_launch_init_minmax(BcCounters* ctr, int n, hipStream_t st);
 // bricks [first, first + count): max_rows bounds each brick's ghosted rows
 // (y * z extent); the encode's max_rows bounds its rows of micro-blocks along x
-// (y * z extent in micro-blocks)
+// (y * z extent in micro-blocks), max_mb0 its micro-blocks along x.  FP8
+// storage: minmax, finalize, encode; otherwise the encode takes the min/max:
+// encode, finalize.
 hipError_t bc_launch_minmax(const BcLoadSrc& src, const BcBrick* bricks, int first, int count, int max_rows,
                             BcCounters* ctr, hipStream_t st);
 hipError_t bc_launch_finalize(BcBrick* bricks, const BcCounters* ctr, int first, int count, int storage,
                               hipStream_t st);
 hipError_t bc_launch_encode(const BcLoadSrc& src, const BcBrick* bricks, int first, int count, int64_t max_rows,
-                            int storage, void* pool, hipStream_t st);
+                            int max_mb0, int storage, void* pool, BcCounters* ctr, hipStream_t st);
 
 struct BcFramePtrs {
   const BcFrameIn* fin;
