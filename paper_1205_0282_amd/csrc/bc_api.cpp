@@ -104,7 +104,7 @@ struct bc_ctx {
   hipEvent_t slot_done[2] = {nullptr, nullptr};
   bool slot_pending[2] = {false, false};
   int ring = 0;
-  hipEvent_t frame_done = nullptr;
+  hipEvent_t frame_done = nullptr;   // the last frame's slot event
   bool frame_pending = false;
   int frame_views = 0;
   // host-source load staging (pinned)
@@ -496,7 +496,6 @@ int bc_create(int hip_device, bc_ctx** out) {
       c->pinned_dev[i] = static_cast<const BcFrameIn*>(dp);
       ok = ok && hipEventCreateWithFlags(&c->slot_done[i], hipEventDisableTiming) == hipSuccess;
     }
-    ok = ok && hipEventCreateWithFlags(&c->frame_done, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking) == hipSuccess;
     ok = ok && hipStreamCreateWithFlags(&c->aux_stream, hipStreamNonBlocking) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&c->fork_ev, hipEventDisableTiming) == hipSuccess;
@@ -527,7 +526,6 @@ void bc_destroy(bc_ctx* c) {
       if (c->slot_done[i]) (void)hipEventDestroy(c->slot_done[i]);
       if (c->pinned[i]) (void)hipHostFree(c->pinned[i]);
     }
-    if (c->frame_done) (void)hipEventDestroy(c->frame_done);
     for (hipEvent_t e : c->tev) (void)hipEventDestroy(e);
     for (GraphSlot& g : c->graphs)
       if (g.exec) (void)hipGraphExecDestroy(g.exec);
@@ -981,12 +979,18 @@ int render_impl(bc_ctx* c, float* out, void* stream, float4* sub, int64_t sub_ca
   }
   // the frame: the kernels of every pass (each pass's set-up kernel first
   // copies the pass inputs from the pinned slot)
+  // a wave takes one work item at a time: no more workgroups than the items
+  // can occupy (a captured frame is replayed for other views: the full count)
+  const bool captured = c->use_graph && !no_alloc;
+  auto workgroups = [&](int64_t items, int most) -> int {
+    return captured ? most : (int)std::min<int64_t>(most, std::max<int64_t>((items + 3) / 4, 1));
+  };
   auto enqueue = [&](hipStream_t s, hipEvent_t* e) -> int {
     if (e && c->timing_stages) HIPCHECK(c, hipEventRecord(e[0], s));
     if (!c->learned) {
       HIPCHECK(c, bc_launch_setup(f, s));
       if (e) HIPCHECK(c, hipEventRecord(e[1], s));
-      HIPCHECK(c, bc_launch_render(f, c->render_workgroups, s));
+      HIPCHECK(c, bc_launch_render(f, workgroups(c->view_tiles, c->render_workgroups), s));
       if (e) HIPCHECK(c, hipEventRecord(e[2], s));
       HIPCHECK(c, bc_launch_composite(f, reinterpret_cast<float4*>(out), s));
     } else {
@@ -1099,7 +1103,7 @@ int render_impl(bc_ctx* c, float* out, void* stream, float4* sub, int64_t sub_ca
   }
   HIPCHECK(c, hipEventRecord(c->slot_done[slot], st));
   c->slot_pending[slot] = true;
-  HIPCHECK(c, hipEventRecord(c->frame_done, st));
+  c->frame_done = c->slot_done[slot];
   c->frame_pending = true;
   c->last_learned = c->learned;
   return BC_OK;
