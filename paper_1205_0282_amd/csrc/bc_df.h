@@ -34,13 +34,13 @@ __device__ __forceinline__ df two_prod(float a, float b) {
   return df_make(p, e);
 }
 
+// a + b with an error of a few 2^-48 of |a| + |b| (the trailing parts are not
+// summed exactly): where a result much smaller than its terms needs no more
+// than the terms' own accuracy, which every use here can say of itself
 __device__ __forceinline__ df df_add(df a, df b) {
 #pragma clang fp contract(off)
   df s = two_sum(a.hi, b.hi);
-  df t = two_sum(a.lo, b.lo);
-  s.lo = s.lo + t.hi;
-  s = fast_two_sum(s.hi, s.lo);
-  s.lo = s.lo + t.lo;
+  s.lo = s.lo + (a.lo + b.lo);
   return fast_two_sum(s.hi, s.lo);
 }
 
@@ -71,31 +71,54 @@ __device__ __forceinline__ df df_add_f(df a, float b) {
   return fast_two_sum(s.hi, s.lo);
 }
 
-// a / b: quotient digits from the hardware reciprocal of b.hi (about 1 ulp),
-// each taken against the exact remainder, so that the approximate reciprocal
-// costs no accuracy; b.hi is a normal number at the call sites (ray
-// directions and lengths of order one)
-__device__ __forceinline__ df df_div(df a, df b) {
+// 1 / a: the hardware reciprocal (about 1 ulp) refined once in FP32, so that
+// an FMA leaves its remainder exact, then corrected by that remainder
+// e = 1 - a r (with the trailing part's product): r (1 + e + e^2), e below
+// 2^-22; a.hi is a normal number at the call sites (ray directions of order
+// one, down to those of nearly axis-parallel rays)
+__device__ __forceinline__ df df_rcp(df a) {
 #pragma clang fp contract(off)
-  const float rb = __builtin_amdgcn_rcpf(b.hi);
-  float q1 = a.hi * rb;
-  df r = df_sub(a, df_mul_f(b, q1));
-  float q2 = r.hi * rb;
-  r = df_sub(r, df_mul_f(b, q2));
-  float q3 = r.hi * rb;
-  df q = fast_two_sum(q1, q2);
-  return df_add_f(q, q3);
+  const float r0 = __builtin_amdgcn_rcpf(a.hi);
+  const float r = __builtin_fmaf(r0, __builtin_fmaf(-a.hi, r0, 1.0f), r0);
+  const float e = __builtin_fmaf(-a.lo, r, __builtin_fmaf(-a.hi, r, 1.0f));
+  return fast_two_sum(r, r * __builtin_fmaf(e, e, e));
 }
 
-__device__ __forceinline__ df df_sqrt(df a) {
+// 1 / sqrt(a): the hardware value r (about 1 ulp) corrected by e = 1 - a r^2:
+// r (1 + e/2 + 3/8 e^2)
+__device__ __forceinline__ df df_rsqrt(df a) {
 #pragma clang fp contract(off)
-  if (a.hi <= 0.0f) return df_from(0.0f);
-  float x = __builtin_amdgcn_sqrtf(a.hi);   // about 1 ulp; the correction below refines it
-  df x2 = two_prod(x, x);
-  df r = df_sub(a, x2);
-  float c = r.hi * (0.5f * __builtin_amdgcn_rcpf(x));
-  return fast_two_sum(x, c);
+  const float r = __builtin_amdgcn_rsqf(a.hi);
+  const df r2 = two_prod(r, r);
+  const df p = two_prod(a.hi, r2.hi);
+  float e = (1.0f - p.hi) - p.lo;
+  e = __builtin_fmaf(-a.hi, r2.lo, e);
+  e = __builtin_fmaf(-a.lo, r2.hi, e);
+  return fast_two_sum(r, r * (e * __builtin_fmaf(0.375f, e, 0.5f)));
 }
+
+// a x + b y + c: exact products and sums of the leading parts, the trailing
+// parts added to their errors
+__device__ __forceinline__ df df_fma2(df a, df x, df b, df y, df c) {
+#pragma clang fp contract(off)
+  const df p = two_prod(a.hi, x.hi), q = two_prod(b.hi, y.hi);
+  const df s = two_sum(p.hi, q.hi), r = two_sum(s.hi, c.hi);
+  const float el = __builtin_fmaf(a.hi, x.lo, a.lo * x.hi), fl = __builtin_fmaf(b.hi, y.lo, b.lo * y.hi);
+  return fast_two_sum(r.hi, ((p.lo + q.lo) + (el + fl)) + ((s.lo + r.lo) + c.lo));
+}
+
+// u.u of a vector
+__device__ __forceinline__ df df_norm2(const df* u) {
+#pragma clang fp contract(off)
+  const df p = two_prod(u[0].hi, u[0].hi), q = two_prod(u[1].hi, u[1].hi), r = two_prod(u[2].hi, u[2].hi);
+  const df s = two_sum(p.hi, q.hi), t = two_sum(s.hi, r.hi);
+  const float l = __builtin_fmaf(u[0].hi, u[0].lo, __builtin_fmaf(u[1].hi, u[1].lo, u[2].hi * u[2].lo));
+  return fast_two_sum(t.hi, __builtin_fmaf(2.0f, l, ((p.lo + q.lo) + r.lo) + (s.lo + t.lo)));
+}
+
+// (f - o) id for a float f (the difference normalised first: near a face its
+// parts are of one size)
+__device__ __forceinline__ df df_plane(float f, df o, df id) { return df_mul(df_add_f(df_neg(o), f), id); }
 
 // exact comparisons of normalised pairs
 __device__ __forceinline__ bool df_lt(df a, df b) { return a.hi < b.hi || (a.hi == b.hi && a.lo < b.lo); }
@@ -103,4 +126,4 @@ __device__ __forceinline__ bool df_ge(df a, df b) { return !df_lt(a, b); }
 __device__ __forceinline__ df df_min(df a, df b) { return df_lt(a, b) ? a : b; }
 __device__ __forceinline__ df df_max(df a, df b) { return df_lt(a, b) ? b : a; }
 
-__device__ __forceinline__ float df_to_f(df a) { return a.hi + a.lo; }
+__device__ __forceinline__ df df_pick(bool c, df a, df b) { return df_make(c ? a.hi : b.hi, c ? a.lo : b.lo); }

@@ -383,31 +383,15 @@ __device__ __forceinline__ int first_index(df t_in, df idt, df t) {
   return (int)fmaxf((j == c && q.lo > 0.0f) ? j + 1.0f : j, 0.0f);
 }
 
-struct Slab { df t0, t1; bool miss; };
-
-// slab test with the reciprocal direction (id[a] valid where d[a] != 0)
-__device__ __forceinline__ Slab slab_df(const df* o, const df* d, const df* id, const float* lo, const float* hi) {
-  Slab s;
-  s.t0 = df_from(-INFINITY);
-  s.t1 = df_from(INFINITY);
-  s.miss = false;
-  for (int a = 0; a < 3; ++a) {
-    if (d[a].hi == 0.0f && d[a].lo == 0.0f) {
-      const bool in = df_ge(o[a], df_from(lo[a])) && df_lt(o[a], df_from(hi[a]));
-      if (!in) s.miss = true;
-      continue;
-    }
-    const df ta = df_mul(df_add_f(df_neg(o[a]), lo[a]), id[a]);
-    const df tb = df_mul(df_add_f(df_neg(o[a]), hi[a]), id[a]);
-    s.t0 = df_max(s.t0, df_min(ta, tb));
-    s.t1 = df_min(s.t1, df_max(ta, tb));
-  }
-  return s;
-}
-
-// 32.32 fixed point of a double-float (each part truncated; error < 2^-31)
+// 32.32 fixed point of a double-float (each part truncated; error < 2^-31).
+// The leading part goes in two steps of 16 bits, each exact, so that no 64-bit
+// conversion (a dozen instructions) is needed; it stays below 2^15 for
+// positions in a brick and for every step that takes two samples in one.
 __device__ __forceinline__ int64_t q32(df a) {
-  return (int64_t)(a.hi * 4294967296.0f) + (int64_t)(a.lo * 4294967296.0f);
+#pragma clang fp contract(off)
+  const float x = a.hi * 65536.0f, t = __builtin_truncf(x);
+  const int lo = (int)((x - t) * 65536.0f) + (int)(a.lo * 4294967296.0f);
+  return (int64_t)(int)t * 65536 + lo;
 }
 
 struct RaySeg {
@@ -423,50 +407,56 @@ __device__ __forceinline__ df df_abs(df a) { return df_lt(a, df_from(0.0f)) ? df
 // is the view's, or with the per-voxel policy 1 / max_a |d_a| (consecutive
 // samples one voxel apart along the ray's dominant axis, the discrete ray
 // casting of Section 2.3.2).
+//
+// Of the cube only the entry is needed: the brick lies inside it, so a ray
+// that misses the cube misses the brick, one behind the eye ends the brick
+// before its first sample, and the brick's exit is never past the cube's (where
+// their faces coincide both come from the same arithmetic).  Every lane does
+// this once per brick its ray may cross, so it is kept short: about 700 vector
+// instructions where general double-float operations took 1900.
 __device__ bool ray_segment(KC(BcViewParams)& vp, const int32_t* gdims, KC(BcBrick)& br, int px, int py,
                             bool per_voxel, RaySeg& seg) {
   const int W = vp.width, H = vp.height;
   const df x = df_mul_f(dfv(vp.iw_hi, vp.iw_lo), (float)(2 * px + 1 - W));
   const df y = df_mul_f(dfv(vp.ih_hi, vp.ih_lo), (float)(H - 2 * py - 1));
-  df o[3], d[3], id[3];
+  df o[3], d[3];
   if (vp.kind == 0) {
     df u[3];
     for (int a = 0; a < 3; ++a) {
       o[a] = dfv(vp.e_hi[a], vp.e_lo[a]);
-      u[a] = df_add(df_add(df_mul(dfv(vp.a_hi[a], vp.a_lo[a]), x), df_mul(dfv(vp.b_hi[a], vp.b_lo[a]), y)),
-                    dfv(vp.c_hi[a], vp.c_lo[a]));
+      u[a] = df_fma2(dfv(vp.a_hi[a], vp.a_lo[a]), x, dfv(vp.b_hi[a], vp.b_lo[a]), y, dfv(vp.c_hi[a], vp.c_lo[a]));
     }
-    const df len = df_sqrt(df_add(df_add(df_mul(u[0], u[0]), df_mul(u[1], u[1])), df_mul(u[2], u[2])));
-    const df ilen = df_div(df_from(1.0f), len);
+    const df ilen = df_rsqrt(df_norm2(u));
     for (int a = 0; a < 3; ++a) d[a] = df_mul(u[a], ilen);
   } else {
     for (int a = 0; a < 3; ++a) {
-      o[a] = df_add(df_add(dfv(vp.e_hi[a], vp.e_lo[a]), df_mul(dfv(vp.a_hi[a], vp.a_lo[a]), x)),
-                    df_mul(dfv(vp.b_hi[a], vp.b_lo[a]), y));
+      o[a] = df_fma2(dfv(vp.a_hi[a], vp.a_lo[a]), x, dfv(vp.b_hi[a], vp.b_lo[a]), y, dfv(vp.e_hi[a], vp.e_lo[a]));
       d[a] = dfv(vp.c_hi[a], vp.c_lo[a]);
     }
   }
-  for (int a = 0; a < 3; ++a)
-    id[a] = (d[a].hi == 0.0f && d[a].lo == 0.0f) ? df_from(0.0f) : df_div(df_from(1.0f), d[a]);
-  const float zero3[3] = {0.0f, 0.0f, 0.0f};
-  const float N3[3] = {(float)gdims[0], (float)gdims[1], (float)gdims[2]};
-  const Slab g = slab_df(o, d, id, zero3, N3);
-  const df t_in = df_max(df_from(0.0f), g.t0);
-  if (g.miss || !df_lt(t_in, g.t1)) return false;
-  const float blo[3] = {(float)br.lo[0], (float)br.lo[1], (float)br.lo[2]};
-  const float bhi[3] = {(float)br.hi[0], (float)br.hi[1], (float)br.hi[2]};
-  const Slab b = slab_df(o, d, id, blo, bhi);
-  if (b.miss || !df_lt(b.t0, b.t1)) return false;
+  // slab tests: entry into the cube, entry into and exit from the brick
+  df g0 = df_from(-INFINITY), b0 = g0, b1 = df_from(INFINITY);
+  bool miss = false;
+  for (int a = 0; a < 3; ++a) {
+    const float blo = (float)br.lo[a], bhi = (float)br.hi[a];
+    // (an axis along which the ray does not move: inside its slab or not at all)
+    const bool still = d[a].hi == 0.0f && d[a].lo == 0.0f;
+    miss = miss || (still && !(df_ge(o[a], df_from(blo)) && df_lt(o[a], df_from(bhi))));
+    const df id = df_rcp(df_make(still ? 1.0f : d[a].hi, d[a].lo));
+    const bool up = d[a].hi > 0.0f;
+    g0 = df_pick(still, g0, df_max(g0, df_plane(up ? 0.0f : (float)gdims[a], o[a], id)));
+    b0 = df_pick(still, b0, df_max(b0, df_plane(up ? blo : bhi, o[a], id)));
+    b1 = df_pick(still, b1, df_min(b1, df_plane(up ? bhi : blo, o[a], id)));
+  }
+  if (miss || !df_lt(b0, b1)) return false;
+  const df t_in = df_max(df_from(0.0f), g0);
   df dt = dfv(vp.dt_hi, vp.dt_lo), idt = dfv(vp.idt_hi, vp.idt_lo);
   if (per_voxel) {
     idt = df_max(df_max(df_abs(d[0]), df_abs(d[1])), df_abs(d[2]));
-    dt = df_div(df_from(1.0f), idt);
+    dt = df_rcp(idt);
   }
-  const int n = first_index(t_in, idt, g.t1);
-  int j0 = (b.t0.hi == -INFINITY) ? 0 : first_index(t_in, idt, b.t0);
-  int j1 = (b.t1.hi == INFINITY) ? n : first_index(t_in, idt, b.t1);
-  j0 = min(j0, n);
-  j1 = min(max(j1, j0), n);
+  // (a ray has a direction: at least one axis took part)
+  const int j0 = first_index(t_in, idt, b0), j1 = first_index(t_in, idt, b1);
   if (j1 <= j0) return false;
   seg.n = j1 - j0;
   const df t0 = df_add(t_in, df_mul_f(dt, (float)j0 + 0.5f));
@@ -602,14 +592,18 @@ __global__ __launch_bounds__(256, 4) void render_kernel(BcFramePtrs f) {
       constexpr uint32_t sh = FMT == 0 ? 2 : (FMT == 1 ? 1 : 0);
       uint32_t dyb = ((uint32_t)mbx * BC_MB_ELEMS - 3u * BC_ROW) << sh,
                dzb = ((uint32_t)mbx * (uint32_t)mby * BC_MB_ELEMS - 12u * BC_ROW) << sh;
-      if (OP == 0) asm volatile("" : "+v"(dyb), "+v"(dzb));   // (selected per lane below)
+      asm volatile("" : "+v"(dyb), "+v"(dzb));   // (selected per lane below)
       // the element index of ghosted local voxel (x, y, z) in the brick: 4x4x4
       // micro-blocks stored row-major, each as 16 rows (y, then z) of 5
       // elements, x fastest.  As a sum of per-axis terms: along x
       // 80 (x>>2) + (x&3) = 20 x - 19 (x&3), along y and z likewise with the
       // micro-block row and slice strides; in bytes
-      const uint32_t cxb = 20u << sh, cyb = (20u * (uint32_t)mbx) << sh, czb = (20u * (uint32_t)mbx * (uint32_t)mby) << sh;
-      const int rxb = -(int)(19u << sh), ryb = (int)(BC_ROW << sh) - (int)cyb, rzb = (int)((4u * BC_ROW) << sh) - (int)czb;
+      const uint32_t cxb = 20u << sh;
+      uint32_t cyb = (20u * (uint32_t)mbx) << sh, czb = (20u * (uint32_t)mbx * (uint32_t)mby) << sh;
+      const int rxb = -(int)(19u << sh);
+      int ryb = (int)(BC_ROW << sh) - (int)cyb, rzb = (int)((4u * BC_ROW) << sh) - (int)czb;
+      // (projection has vector registers to spare and no scalar ones)
+      if (OP == 1) asm volatile("" : "+v"(cyb), "+v"(czb), "+v"(ryb), "+v"(rzb));
       int64_t uc0 = seg.u[0], uc1 = seg.u[1], uc2 = seg.u[2];
       // the step, with y and z scaled by 4 and 16 (kept only so, to save
       // registers) so that in the occupancy pass bits 2-3 of the integer part
