@@ -69,30 +69,22 @@ hipError_t bc_launch_composite(const BcFramePtrs& f, float4* out, hipStream_t st
 hipError_t bc_launch_psnr(const BcFramePtrs& f, const float4* ref, const float4* img, hipStream_t st);
 
 // Queue order of the (brick, view) entries: bricks grouped by b % Q, then b,
-// then view.  Returns the position of entry (b, v) and, inversely, the entry at
-// a position.
+// then view: the bricks of a group, and the entry at a position.
 __device__ __forceinline__ int group_size(int nb, int Q, int x) { return x < nb ? (nb - x + Q - 1) / Q : 0; }
-__device__ __forceinline__ int queue_pos(int b, int v, int nb, int nv, int Q) {
-  const int x = b % Q;
-  int before = 0;
-  for (int g = 0; g < x; ++g) before += group_size(nb, Q, g);
-  return (before + b / Q) * nv + v;
-}
 __device__ __forceinline__ void queue_entry(int pos, int nb, int nv, int Q, int& b, int& v) {
-  const int e = pos / nv;
-  v = pos % nv;
-  int cum = 0, x = 0;
-  for (; x < Q - 1; ++x) {
-    const int g = group_size(nb, Q, x);
-    if (e < cum + g) break;
-    cum += g;
-  }
-  b = x + (e - cum) * Q;
+  const uint32_t e = (uint32_t)pos / (uint32_t)nv;
+  v = pos - (int)e * nv;
+  // the first `more` groups hold one brick more than the others
+  const uint32_t size = (uint32_t)nb / (uint32_t)Q, more = (uint32_t)nb - size * (uint32_t)Q, big = more * (size + 1);
+  const uint32_t r = e < big ? e : e - big, s = e < big ? size + 1 : size;   // (s > 0: e is an entry)
+  const uint32_t g = r / s;
+  b = (int)((e < big ? g : more + g) + (r - g * s) * (uint32_t)Q);
 }
 
 // tile selection {t : t % s == o}: first selected tile >= lo, count in [lo, hi)
-__device__ __forceinline__ int sel_first(int lo, int s, int o) { return lo + ((o - lo) % s + s) % s; }
+__device__ __forceinline__ int sel_first(int lo, int s, int o) { return s == 1 ? lo : lo + ((o - lo) % s + s) % s; }
 __device__ __forceinline__ int sel_count(int lo, int hi, int s, int o) {
+  if (s == 1) return max(hi - lo, 0);
   const int f = sel_first(lo, s, o);
   return f < hi ? (hi - 1 - f) / s + 1 : 0;
 }
