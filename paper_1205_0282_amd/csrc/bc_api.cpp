@@ -74,6 +74,16 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 constexpr int kMaxTimedFrames = 4096;
 constexpr int kPasses = 3;   // learned frame: coarse, validation, conditional plain
 
+// Where the ray caster's two forms meet, in work items times a brick's edge in
+// samples (render us, persistent / four lanes to a ray, FP32 compositing):
+// 128^3 bricks 9.7 K items 227 / 180, 15 K 260 / 251, 20 K 295 / 309; 250^3
+// bricks 2.9 K items 390 / 232, 9.2 K 256 / 277; 64^3 bricks 25 K items
+// 221 / 191; FP16 100^3 bricks 14 K items 223 / 188, 30 K 300 / 362.
+constexpr double kQuadSamples = 4.7e6;
+// Projection at one sample per voxel: 256^3 bricks, 82 K items, FP32 1505 /
+// 1384, FP16 1234 / 1177, FP8 1052 / 1078; 125^3 bricks, 71 K items, FP32 569 / 630.
+constexpr double kQuadMipEdge = 192.0;
+
 }  // namespace
 
 struct bc_ctx {
@@ -840,18 +850,12 @@ int bc_set_view(bc_ctx* c, const bc_view* views, int n) {
       return fail(c, BC_E_ARG, "bc_set_view: frame %d x %d exceeds the planned %d x %d", views[i].width,
                   views[i].height, c->max_w, c->max_h);
   }
-  if (c->planned) {
-    int64_t tiles = 0;
-    for (int i = 0; i < n; ++i) tiles += view_tiles_bound(c, views[i]);
-    if (tiles > c->max_tiles)
-      return fail(c, BC_E_NOMEM, "bc_set_view: the views need up to %lld sub-image tiles, %lld planned",
-                  (long long)tiles, (long long)c->max_tiles);
-  }
-  {
-    int64_t tiles = 0;
-    for (int i = 0; i < n; ++i) tiles += view_tiles_bound(c, views[i]);
-    c->view_tiles = tiles;
-  }
+  int64_t tiles = 0;
+  for (int i = 0; i < n; ++i) tiles += view_tiles_bound(c, views[i]);
+  if (c->planned && tiles > c->max_tiles)
+    return fail(c, BC_E_NOMEM, "bc_set_view: the views need up to %lld sub-image tiles, %lld planned",
+                (long long)tiles, (long long)c->max_tiles);
+  c->view_tiles = tiles;
   c->views.assign(views, views + n);
   c->has_view = true;
   return BC_OK;
@@ -947,9 +951,8 @@ int render_impl(bc_ctx* c, float* out, void* stream, float4* sub, int64_t sub_ca
   // learned frames: sub-image tiles for a concurrent validation pass, if the
   // coarse pass and the validation pass fit the buffer together (else the
   // passes run one after the other)
-  int64_t split = 0;
+  int64_t split = 0, coarse_tiles = 0, val_tiles = 0;
   if (c->learned) {
-    int64_t coarse_tiles = 0, val_tiles = 0;
     for (int i = 0; i < n; ++i) {
       coarse_tiles += view_tiles_bound(c, c->views[i], W / 2, H / 2, 1);
       val_tiles += view_tiles_bound(c, c->views[i], W, H, c->val_stride);
@@ -970,6 +973,7 @@ int render_impl(bc_ctx* c, float* out, void* stream, float4* sub, int64_t sub_ca
   BcFramePtrs f = frame_ptrs(c);
   f.sub = sub;
   f.max_items = sub_cap;
+  f.item_bound = 0;
   // each pass's set-up kernel copies that pass's inputs from the slot
   f.fin_src = c->pinned_dev[slot];
   f.fin_bytes = (int32_t)fin_bytes;
@@ -985,9 +989,27 @@ int render_impl(bc_ctx* c, float* out, void* stream, float4* sub, int64_t sub_ca
   auto workgroups = [&](int64_t items, int most) -> int {
     return captured ? most : (int)std::min<int64_t>(most, std::max<int64_t>((items + 3) / 4, 1));
   };
+  // Few samples in all, and a workgroup takes each item with four lanes to a
+  // ray (render_quad_kernel) instead of the persistent launch, whose time is
+  // then that of a few long items.  `items` bounds the pass's items; a ray
+  // crosses a brick in up to about an edge's worth of samples.
+  double edge = 0.0;
+  for (int a = 0; a < 3; ++a)
+    edge += (double)std::min<int64_t>(c->desc.brick_dims[a], c->desc.share_hi[a] - c->desc.share_lo[a]) / 3.0;
+  auto route = [&](BcFramePtrs& p, int64_t items, double step) {
+    const double per_ray = edge / (c->step_policy == BC_STEP_PER_VOXEL ? 1.0 : step);
+    // (projection at one sample per voxel through large bricks, from FP32 and
+    // FP16: its rays gather so few samples per line that the quads' better
+    // spread pays at any size)
+    const bool sparse = c->op == BC_OP_MIP && c->step_policy == BC_STEP_PER_VOXEL && c->desc.storage != BC_FP8_E4M3 &&
+                        edge >= kQuadMipEdge;
+    const bool quad = !captured && c->chunk == 32 && ((double)items * per_ray <= kQuadSamples || sparse);
+    p.item_bound = quad ? std::min<int64_t>(std::max<int64_t>(items, 1), 1 << 20) : 0;
+  };
   auto enqueue = [&](hipStream_t s, hipEvent_t* e) -> int {
     if (e && c->timing_stages) HIPCHECK(c, hipEventRecord(e[0], s));
     if (!c->learned) {
+      route(f, c->view_tiles, dt);
       HIPCHECK(c, bc_launch_setup(f, s));
       if (e) HIPCHECK(c, hipEventRecord(e[1], s));
       HIPCHECK(c, bc_launch_render(f, workgroups(c->view_tiles, c->render_workgroups), s));
@@ -999,6 +1021,8 @@ int render_impl(bc_ctx* c, float* out, void* stream, float4* sub, int64_t sub_ca
       float* val_img = reinterpret_cast<float*>(c->cnn_ws + L.val);
       BcFramePtrs fc = pass_ptrs(c, f, 0, W / 2, H / 2);
       BcFramePtrs fv = pass_ptrs(c, f, 1, W, H);
+      route(fc, coarse_tiles, c->coarse_step);
+      route(fv, val_tiles, dt);
       if (split > 0) {
         // the validation pass has few work items, each a long walk through a
         // brick: it runs on the second stream, on its own arrays, sub-image
@@ -1172,6 +1196,10 @@ int bc_get_frame_stats(bc_ctx* c, bc_frame_stats* s) {
   HIPCHECK(c, hipMemcpy(&h, meta + c->off_ctr, offsetof(BcCounters, minmax), hipMemcpyDeviceToHost));
   s->nominal_samples = h.nominal;
   s->evaluated_samples = h.evaluated;
+  for (const BcCountPart& p : h.part) {
+    s->nominal_samples += p.count[0];
+    s->evaluated_samples += p.count[1];
+  }
   s->n_tiles = h.total_items;
   s->fell_back = c->last_learned ? (int32_t)h.fallback : -1;
   s->psnr_db = c->last_learned ? h.psnr_db : NAN;

@@ -411,6 +411,8 @@ __device__ void setup_items(const BcFramePtrs& f, bool skip, int32_t* spart) {
     }
   }
   __syncthreads();
+  if (f.fin->reset_counters && tid >= 64 && tid < 64 + 2 * BC_COUNT_PARTS)
+    f.ctr->part[(tid - 64) >> 1].count[tid & 1] = 0ull;
   if (tid < 8) {
     f.ctr->q[tid].next = 0u;
     int g0 = 0;

@@ -49,6 +49,7 @@ struct BcFramePtrs {
   int32_t n_bricks, n_views;
   int32_t gdims[3];
   int64_t max_items;
+  int64_t item_bound;     // ray caster with a workgroup per item: the bound on the items (0: persistent)
   int32_t storage;
   int32_t width, height;  // frame size (all views share it)
   int32_t urgent;         // 1: the ray caster's waves issue at raised priority (2, and 3 while

@@ -869,9 +869,245 @@ __global__ __launch_bounds__(256, 4) void render_kernel(BcFramePtrs f) {
   }
 }
 
+// ------------------------------------------------------------------ render, few work items
+// A frame of few work items leaves most of the chip idle while each wave walks
+// a whole tile: its time is one wave's chain of dependent gathers.  Here a
+// workgroup takes one item, a wave 16 of its rays, and four neighbouring lanes
+// one ray: they gather a quarter of a chunk's occupancy bits each, evaluate four
+// occupied samples at a time, and each folds all four colours in order, so that
+// images, counts and early termination are those of render_kernel bit for bit.
+// No queue: the launch has about a workgroup per item.  61x47 frame of a
+// 37x29x23 cube 19.4 -> 13.3 us, 256x256 of 128^3 63 -> 31; with enough items
+// to fill the chip the persistent kernel's waves, each with 64 rays, do the
+// same in fewer instructions (1024^3 frame 1308 against 1994 us).
+template <int J>
+__device__ __forceinline__ float quad_lane(float v) {   // lane J of the lane's four
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x55 * J, 0xf, 0xf, true));
+}
+
+template <int FMT, bool TF_LDS, int OP>
+__global__ __launch_bounds__(256) void render_quad_kernel(BcFramePtrs f) {
+  extern __shared__ float4 q_tab[];   // table entry k at 2k, its difference to entry k+1 at 2k+1
+  __shared__ uint32_t wave_count[2][4];
+  KC(BcFrameIn)* fin = kc(f.fin);
+  KC(BcCounters)* cr = kc(f.ctr);
+  const uint32_t n_items = cr->n_items;
+  if (blockIdx.x >= n_items) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = (int)__builtin_amdgcn_readfirstlane(tid >> 6), sub = lane & 3;
+  const int K = fin->K;
+  const float4* gtab = reinterpret_cast<const float4*>(f.fin->table);
+  // (on its way during the ray set-up)
+  float4 ta = make_float4(0.f, 0.f, 0.f, 0.f), tb = ta;
+  if (TF_LDS && OP == 0 && tid < K) {
+    ta = gtab[tid];
+    tb = gtab[min(tid + 1, K - 1)];
+  }
+  const float tf_scale = fin->tf_scale, tf_bias = fin->tf_bias, kmax_f = (float)(K - 1);
+  uint32_t nominal = 0, evaluated = 0;
+  bool staged = false;
+  for (uint32_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+    KC(int32_t)* perm = kc(f.item_perm);
+    int lo = 0, hi = f.n_bricks * f.n_views;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if ((uint32_t)perm[mid] <= item) lo = mid; else hi = mid;
+    }
+    KC(int4)& ent = kc(f.item_entry)[lo];
+    const int b = ent.x & 0xffff, v = ent.x >> 16, cx = ent.y, ts = fin->tile_stride;
+    const int local = (int)(item - (uint32_t)perm[lo]);
+    const int tx = ent.z + (local % cx) * ts, ty = ent.w + (local / cx) * ts;
+    KC(BcViewParams)& vp = kc(f.views)[v];
+    KC(BcBrick)& br = kc(f.bricks)[b];
+    const int tsh = f.tile_shift, pix = 16 * wave + (lane >> 2);
+    const int px = (tx << tsh) + (pix & ((1 << tsh) - 1)), py = ty * (64 >> tsh) + (pix >> tsh);
+    RaySeg seg;
+    const bool hit = px < vp.width && py < vp.height && ray_segment(vp, f.gdims, br, px, py, f.step_policy != 0, seg);
+    if (TF_LDS && OP == 0 && !staged) {
+      staged = true;
+      for (int k = tid; k < K; k += 256) {
+        if (k != tid) {
+          ta = gtab[k];
+          tb = gtab[min(k + 1, K - 1)];
+        }
+        q_tab[2 * k] = ta;
+        q_tab[2 * k + 1] = make_float4(tb.x - ta.x, tb.y - ta.y, tb.z - ta.z, tb.w - ta.w);
+      }
+      __syncthreads();
+    }
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    float mx = -INFINITY;
+    if (hit) {
+      constexpr uint32_t esz = FMT == 0 ? 4 : (FMT == 1 ? 2 : 1);
+      constexpr uint32_t sh = FMT == 0 ? 2 : (FMT == 1 ? 1 : 0);
+      constexpr bool FOLD = FMT == 2 && OP == 0;
+      const float tau = vp.tau, bound = br.dmax;
+      mx = -FLT_MAX;
+      // strides and resources as in render_kernel
+      const uint32_t mbx = (uint32_t)br.mb[0], mby = (uint32_t)br.mb[1];
+      const uint32_t WX = (uint32_t)br.occ_w[0], WY = (uint32_t)br.occ_w[1], WX4 = 4u * WX;
+      const __amdgpu_buffer_rsrc_t occ = make_rsrc(f.occ + br.occ_offset, WX * WY * (uint32_t)br.occ_w[2] * 4u);
+      const __amdgpu_buffer_rsrc_t pool = make_rsrc(static_cast<const char*>(f.pool) + br.offset * esz,
+                                                    mbx * mby * (uint32_t)br.mb[2] * BC_MB_ELEMS * esz);
+      const float s_q = br.scale, o_q = br.offs;
+      const float tsc = FOLD ? tf_scale * s_q : tf_scale, tbi = FOLD ? __builtin_fmaf(o_q, tf_scale, tf_bias) : tf_bias;
+      const uint32_t dyb = (mbx * BC_MB_ELEMS - 3u * BC_ROW) << sh, dzb = (mbx * mby * BC_MB_ELEMS - 12u * BC_ROW) << sh;
+      const uint32_t cxb = 20u << sh, cyb = (20u * mbx) << sh, czb = (20u * mbx * mby) << sh;
+      const int rxb = -(int)(19u << sh), ryb = (int)(BC_ROW << sh) - (int)cyb, rzb = (int)((4u * BC_ROW) << sh) - (int)czb;
+      int64_t uc0 = seg.u[0], uc1 = seg.u[1], uc2 = seg.u[2];
+      const int64_t s0 = seg.s[0], s1 = seg.s[1], s2 = seg.s[2];
+      const float sfx = (float)s0 * 2.3283064365386963e-10f, sfy = (float)s1 * 2.3283064365386963e-10f,
+                  sfz = (float)s2 * 2.3283064365386963e-10f;
+      int used = seg.n;
+      for (int k = 0; k < seg.n; k += 32) {
+        const int cnt = min(32, seg.n - k);
+        uint32_t mask = cnt >= 32 ? ~0u : (1u << cnt) - 1u;
+        if (f.ess) {
+          // the lane's eight samples; the words all in flight together
+          int64_t un0 = uc0 + 8 * sub * s0, un1 = (uc1 + 8 * sub * s1) * 4, un2 = (uc2 + 8 * sub * s2) * 16;
+          uint32_t bit[8], ofs[8], word[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const uint32_t ix = (uint32_t)hi32(un0), iy4 = (uint32_t)hi32(un1), iz16 = (uint32_t)hi32(un2);
+            ofs[i] = mad_u24(mad_u24(iz16 >> 5, WY, iy4 >> 4), WX4, ix & ~3u);
+            bit[i] = bfi_u32(15u, bfi_u32(3u, ix, iy4), iz16);
+            un0 += s0; un1 += 4 * s1; un2 += 16 * s2;
+          }
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            word[i] = __builtin_amdgcn_raw_buffer_load_b32(occ, i && ofs[i] == ofs[i - 1] ? 0xfffffff0u : ofs[i], 0, 0);
+          uint32_t m = 0, w = 0;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            w = word[i] | (i && ofs[i] == ofs[i - 1] ? w : 0u);
+            m |= __builtin_amdgcn_ubfe(w, bit[i], 1u) << i;
+          }
+          m <<= 8 * sub;
+          m |= (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0xb1, 0xf, 0xf, true);   // lane ^ 1
+          m |= (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x4e, 0xf, 0xf, true);   // lane ^ 2
+          mask &= m;
+        }
+        const int bx = hi32(uc0), by = hi32(uc1), bz = hi32(uc2);
+        const float fx0 = frac32(uc0), fy0 = frac32(uc1), fz0 = frac32(uc2);
+        int last = 31;
+        bool stop = false;
+        uint32_t left = mask;
+        while (left) {
+          // the four lowest samples left, one to a lane (the last one again where there are fewer)
+          int idx[4];
+          bool on[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            on[j] = left != 0u;
+            idx[j] = on[j] ? (int)__builtin_ctz(left) : idx[j > 0 ? j - 1 : 0];
+            left &= left - 1u;
+          }
+          const int i = sub == 0 ? idx[0] : (sub == 1 ? idx[1] : (sub == 2 ? idx[2] : idx[3]));
+          const float fi = (float)i;
+          const float ux = __builtin_fmaf(fi, sfx, fx0), uy = __builtin_fmaf(fi, sfy, fy0), uz = __builtin_fmaf(fi, sfz, fz0);
+          const float wx = __builtin_amdgcn_fractf(ux), wy = __builtin_amdgcn_fractf(uy), wz = __builtin_amdgcn_fractf(uz);
+          const uint32_t ix = (uint32_t)(bx + floor_i32(ux)), iy = (uint32_t)(by + floor_i32(uy)),
+                         iz = (uint32_t)(bz + floor_i32(uz));
+          const int ry = (int)(iy & 3u), rz = (int)(iz & 3u);
+          const uint32_t a000 = (uint32_t)mad_i24(
+              rz, rzb, mad_i24(ry, ryb, mad_i24((int)(ix & 3u), rxb, (int)mad_u24(ix, cxb, mad_u24(iy, cyb, __umul24(iz, czb))))));
+          const uint32_t dy = ry == 3 ? dyb : (BC_ROW << sh), dz = rz == 3 ? dzb : ((4u * BC_ROW) << sh);
+          float c[8];
+          load_pair<FOLD ? 3 : FMT>(pool, a000, s_q, o_q, c[0], c[1]);
+          load_pair<FOLD ? 3 : FMT>(pool, a000 + dy, s_q, o_q, c[2], c[3]);
+          load_pair<FOLD ? 3 : FMT>(pool, a000 + dz, s_q, o_q, c[4], c[5]);
+          load_pair<FOLD ? 3 : FMT>(pool, a000 + dz + dy, s_q, o_q, c[6], c[7]);
+          const float c00 = __builtin_fmaf(wx, c[1] - c[0], c[0]), c10 = __builtin_fmaf(wx, c[3] - c[2], c[2]);
+          const float c01 = __builtin_fmaf(wx, c[5] - c[4], c[4]), c11 = __builtin_fmaf(wx, c[7] - c[6], c[6]);
+          const float c0 = __builtin_fmaf(wy, c10 - c00, c00), c1 = __builtin_fmaf(wy, c11 - c01, c01);
+          const float val = __builtin_fmaf(wz, c1 - c0, c0);
+          if (OP == 1) {
+            const float val4[4] = {quad_lane<0>(val), quad_lane<1>(val), quad_lane<2>(val), quad_lane<3>(val)};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              if (!on[j] || stop) continue;
+              mx = fmaxf(mx, val4[j]);
+              if (mx >= bound) {
+                last = idx[j];
+                stop = true;
+              }
+            }
+          } else {
+            const float xt = __builtin_amdgcn_fmed3f(__builtin_fmaf(val, tsc, tbi), 0.0f, kmax_f);
+            const int it = TF_LDS ? (int)xt : min((int)xt, K - 2);
+            const float ft = TF_LDS ? __builtin_amdgcn_fractf(xt) : xt - (float)it;
+            float4 q0, dq;
+            if (TF_LDS) {
+              q0 = q_tab[2 * it];
+              dq = q_tab[2 * it + 1];
+            } else {
+              q0 = gtab[it];
+              const float4 q1 = gtab[it + 1];
+              dq = make_float4(q1.x - q0.x, q1.y - q0.y, q1.z - q0.z, q1.w - q0.w);
+            }
+            const float4 col = make_float4(__builtin_fmaf(ft, dq.x, q0.x), __builtin_fmaf(ft, dq.y, q0.y),
+                                           __builtin_fmaf(ft, dq.z, q0.z), __builtin_fmaf(ft, dq.w, q0.w));
+            const float4 col4[4] = {
+                make_float4(quad_lane<0>(col.x), quad_lane<0>(col.y), quad_lane<0>(col.z), quad_lane<0>(col.w)),
+                make_float4(quad_lane<1>(col.x), quad_lane<1>(col.y), quad_lane<1>(col.z), quad_lane<1>(col.w)),
+                make_float4(quad_lane<2>(col.x), quad_lane<2>(col.y), quad_lane<2>(col.z), quad_lane<2>(col.w)),
+                make_float4(quad_lane<3>(col.x), quad_lane<3>(col.y), quad_lane<3>(col.z), quad_lane<3>(col.w))};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              if (!on[j] || stop) continue;
+              const float om = 1.0f - acc.w;
+              acc.x = __builtin_fmaf(om, col4[j].x, acc.x);
+              acc.y = __builtin_fmaf(om, col4[j].y, acc.y);
+              acc.z = __builtin_fmaf(om, col4[j].z, acc.z);
+              acc.w = __builtin_fmaf(om, col4[j].w, acc.w);
+              if (acc.w >= tau) {
+                last = idx[j];
+                stop = true;
+              }
+            }
+          }
+          if (stop) left = 0u;
+        }
+        if (sub == 0) evaluated += (uint32_t)__builtin_popcount(mask & (~0u >> (31 - last)));
+        if (stop) {
+          used = k + last + 1;
+          break;
+        }
+        uc0 += 32 * s0; uc1 += 32 * s1; uc2 += 32 * s2;
+      }
+      if (sub == 0) nominal += (uint32_t)used;
+    }
+    if (sub == 0) {
+      if (OP == 0) f.sub[(int64_t)item * 64 + pix] = acc;
+      else reinterpret_cast<float*>(f.sub)[(int64_t)item * 64 + pix] = mx;
+    }
+  }
+  // one addition per workgroup, spread over a few cache lines
+  for (int off = 32; off > 0; off >>= 1) {
+    nominal += __shfl_xor(nominal, off);
+    evaluated += __shfl_xor(evaluated, off);
+  }
+  if (lane == 0) {
+    wave_count[0][wave] = nominal;
+    wave_count[1][wave] = evaluated;
+  }
+  __syncthreads();
+  if (tid < 2) {
+    unsigned long long n = 0;
+    for (int w = 0; w < 4; ++w) n += wave_count[tid][w];
+    if (n) atomicAdd(&f.ctr->part[blockIdx.x % BC_COUNT_PARTS].count[tid], n);
+  }
+}
+
 template <int FMT>
 hipError_t launch_render_fmt(const BcFramePtrs& f, int n_workgroups, hipStream_t st) {
   const bool lds = f.K <= BC_TF_LDS;
+  if (f.item_bound > 0) {
+    const int n = (int)f.item_bound;   // (a further item, if the bound were short, is a workgroup's second)
+    if (f.op == 1) render_quad_kernel<FMT, false, 1><<<n, 256, 0, st>>>(f);
+    else if (lds) render_quad_kernel<FMT, true, 0><<<n, 256, sizeof(float4) * 2 * f.K, st>>>(f);
+    else render_quad_kernel<FMT, false, 0><<<n, 256, 0, st>>>(f);
+    return hipGetLastError();
+  }
   if (f.op == 1) {
     // the colour map is applied after the merge: no table in the ray caster
     if (f.chunk == 32) render_kernel<FMT, false, 32, 1, false><<<n_workgroups, 256, 0, st>>>(f);

@@ -90,6 +90,11 @@ struct BcQueueCounter {
   uint32_t next;             // next item of the queue (relative to its start)
   uint32_t pad_[31];
 };
+#define BC_COUNT_PARTS 16
+struct BcCountPart {
+  unsigned long long count[2];   // nominal, evaluated
+  uint32_t pad_[28];
+};
 struct BcCounters {
   // written by the set-up kernel, read-only during ray casting
   uint32_t n_items;          // work items of the pass
@@ -104,9 +109,11 @@ struct BcCounters {
   unsigned long long evaluated;
   uint32_t pad1_[28];
   BcQueueCounter q[8];
+  BcCountPart part[BC_COUNT_PARTS];    // further shares of the sample counts (launches of a workgroup per item)
   uint32_t minmax[BC_MAX_BRICKS][2];   // load time: ordered-int min/max per brick
 };
 
 static_assert(offsetof(BcCounters, nominal) == 128, "sample counts start a cache line");
 static_assert(offsetof(BcCounters, q) == 256, "queue counters start a cache line");
 static_assert(sizeof(BcQueueCounter) == 128, "one queue counter per cache line");
+static_assert(sizeof(BcCountPart) == 128, "one share of the sample counts per cache line");
