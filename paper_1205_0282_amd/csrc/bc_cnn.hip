@@ -8,9 +8,9 @@
 // Every convolution is an implicit GEMM on the matrix cores: rows are output
 // pixels, columns output channels, and the reduction runs over (tap, input
 // channel) in steps of 32 with v_mfma_f32_16x16x32_bf16 (BF16 operands, FP32
-// accumulation).  Operand B (weights) is pre-packed per (k-step, n-tile) in
-// the lane order of the instruction, so one 16-byte load per lane feeds one
-// MFMA.  Operand A is read from an LDS tile of the layer input (NHWC, BF16).
+// accumulation).  The weights are pre-packed per (k-step, n-tile) in the lane
+// order of the instruction, so one 16-byte load per lane fetches a fragment.
+// The pixels are read from an LDS tile of the layer input (NHWC, BF16).
 //
 // Kernels: fused inference (all three layers of a 16x16 output tile with
 // LDS-resident activations), per-layer training forward with the loss in the
@@ -37,8 +37,8 @@ __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
-// ------------------------------------------------------------------ A operand
-// Lane (g = lane/16, r = lane%16) of an M-tile supplies row r (output pixel p)
+// ------------------------------------------------------------------ pixel operand
+// Lane (g = lane/16, r = lane%16) of an M-tile supplies pixel r (output pixel p)
 // and reduction indices k0 .. k0+7 with k0 = 32 ks + 8 g; k = tap*CIN + c.
 // `in` is an LDS tile, WIN pixels wide, SIN BF16 elements per pixel; the
 // output pixel with input offset `pix` (its element index in the tile) reads
@@ -84,24 +84,34 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_rsrc(const void* base, ui
   return __builtin_amdgcn_make_buffer_rsrc(ub, (short)0, (int)bytes, 0x00020000);
 }
 
+// a layer's packed weights in registers: one 16-byte load per lane and fragment
+// (through a buffer resource: one lane offset, the fragments' are constants)
+template <int N>
+__device__ __forceinline__ void load_weights(const uint4* __restrict__ wf, bf16x8 (&w)[N]) {
+  typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+  const __amdgpu_buffer_rsrc_t wr = wave_rsrc(wf, (uint32_t)(N * 64 * 16));
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    w[i] = __builtin_bit_cast(bf16x8, (u4)__builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, i * 1024, 0));
+}
+
 // One convolution layer over an LDS tile: M output pixels in raster order of
-// an output tile WOUT wide; KS k-steps, NT n-tiles of packed weights `wf`
-// (read through a buffer resource: one lane offset, the fragment offsets are
-// constants).  A wave takes R of its M-tiles at a time, so that every weight
-// fragment it loads feeds R matrix instructions (and R x NT accumulations are
-// in flight).  epi(p0, v) receives the accumulated outputs (bias not added)
-// of four consecutive pixels p0 .. p0+3 (those below M are valid): v[nt][i] is
-// pixel p0 + i, channel 16 nt + (lane % 16); per-pixel work is done once for
-// all the lane's channels.
+// an output tile WOUT wide; KS k-steps, NT n-tiles of weights `w`.  The weights
+// stay in registers: read again for each pair of M-tiles they took more of the
+// L1's 64 bytes a cycle than the matrix cores left it.  A wave takes R of its
+// M-tiles at a time (R x NT accumulations in flight).  The weights are the
+// first operand, so that a lane ends up with four consecutive channels of one
+// pixel: epi(p, v) receives them for pixel p < M (bias not added), v[nt][i] of
+// channel 16 nt + 4 (lane / 16) + i.
 template <int CIN, int KS, int NT, int R, int WIN, int SIN, int M, int WOUT, typename Epi>
-__device__ __forceinline__ void conv_tile(const uint16_t* in, const uint4* __restrict__ wf, Epi epi) {
+__device__ __forceinline__ void conv_tile(const uint16_t* in, const bf16x8 (&w)[KS * NT], Epi epi) {
   // (every kernel here runs 256-thread workgroups: 4 waves; the wave index is
   // made explicitly uniform so that the per-tile guards below are scalar branches)
   constexpr int nwaves = 4;
   const int lane = threadIdx.x & 63, wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, r = lane & 15;
   constexpr int n_mt = (M + 15) / 16;
-  const __amdgpu_buffer_rsrc_t wr = wave_rsrc(wf, (uint32_t)(KS * NT * 64 * 16));
   // the lane's tap offsets do not depend on the pixel: computed once
   int2 off[KS];
 #pragma unroll
@@ -116,143 +126,143 @@ __device__ __forceinline__ void conv_tile(const uint16_t* in, const uint4* __res
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) acc[j][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
+    // (every slot is computed: a slot past the last M-tile reads clamped
+    // pixels and is not stored; a guard here would cost more than it saves)
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       bf16x8 a[R];
 #pragma unroll
       for (int j = 0; j < R; ++j) a[j] = load_a<CIN>(in, pix[j], off[ks]);
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-        const u4 w = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, (ks * NT + nt) * 1024, 0);
-        const bf16x8 b = __builtin_bit_cast(bf16x8, w);
-        // (every slot is computed: a slot past the last M-tile reads clamped
-        // pixels and is not stored; a guard here would cost more than it saves)
+      for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int j = 0; j < R; ++j) acc[j][nt] = mfma(a[j], b, acc[j][nt]);
-      }
+        for (int j = 0; j < R; ++j) acc[j][nt] = mfma(w[ks * NT + nt], a[j], acc[j][nt]);
     }
 #pragma unroll
     for (int j = 0; j < R; ++j) {
       const int mt = base + nwaves * j;
       if (mt >= n_mt) break;
-      epi(mt * 16 + 4 * g, acc[j]);
+      const int p = mt * 16 + r;
+      if (p < M) epi(p, acc[j]);
     }
   }
 }
 
-// fine-pixel value of the bilinear x2 upsampling of channel c of x (FP32,
-// half-pixel centres, clamp to edge)
-__device__ __forceinline__ float bilinear2(const float* __restrict__ x, int H, int W, int Y, int X, int c) {
-  const float cy = ((float)Y + 0.5f) * 0.5f - 0.5f, cx = ((float)X + 0.5f) * 0.5f - 0.5f;
-  const float fy0 = floorf(cy), fx0 = floorf(cx);
-  const float fy = cy - fy0, fx = cx - fx0;
-  const int y0 = min(max((int)fy0, 0), H - 1), y1 = min(max((int)fy0 + 1, 0), H - 1);
-  const int x0 = min(max((int)fx0, 0), W - 1), x1 = min(max((int)fx0 + 1, 0), W - 1);
-  const float v00 = x[((int64_t)y0 * W + x0) * 4 + c], v01 = x[((int64_t)y0 * W + x1) * 4 + c];
-  const float v10 = x[((int64_t)y1 * W + x0) * 4 + c], v11 = x[((int64_t)y1 * W + x1) * 4 + c];
-  const float top = v00 * (1.0f - fx) + v01 * fx;
-  const float bot = v10 * (1.0f - fx) + v11 * fx;
-  return top * (1.0f - fy) + bot * fy;
+// four values as BF16
+__device__ __forceinline__ uint2 bf16_pack(float a, float b, float c, float d) {
+  return make_uint2(bf16_bits(a) | (uint32_t)bf16_bits(b) << 16, bf16_bits(c) | (uint32_t)bf16_bits(d) << 16);
 }
 
-constexpr int PSTRIDE = 32;   // BF16 elements per pixel of a 32-channel LDS tile (64 B, 16-B aligned): the fused
-                               // inference then takes 51 KB of LDS, so three workgroups fit a CU (45.8 us per
-                               // 960x540 frame, against 52.2 us with 80-B pixels and two workgroups, despite
-                               // more bank conflicts)
+constexpr int PSTRIDE = 40;   // BF16 elements per pixel of a 32-channel LDS tile: 80 bytes, so that the 16 pixels
+                               // that a 16-byte read touches start 4 banks apart and cover all banks once
 
 // ------------------------------------------------------------------ inference
 // One 16x16 tile of coarse pixels per workgroup: input tile with a 3-pixel
-// halo, both hidden activations in LDS, output 32x32 fine pixels.  The last
+// halo, both hidden activations in LDS, output 32x32 fine pixels.  The next
+// layer's weights are on their way to registers during a layer.  The last
 // layer's results go to an LDS output tile (in the first activation's space,
 // free by then) and leave as whole fine pixels, with the bilinear skip read
 // from an FP32 copy of the input (in the BF16 input tile's space, free after
-// the first layer).
-constexpr int XF = 18;   // FP32 input pixels per side for the bilinear skip of a tile
-__global__ __launch_bounds__(256) void infer_kernel(CnnInferArgs a) {
+// the first layer).  Bound by the latency of its phases (matrix cores busy 18%,
+// LDS 35% of the cycles): 960x540 takes 39.7 us, 44.0 with the pixels as the
+// first operand (single 16-bit stores of the activations) and the weights read
+// again for every few M-tiles; a workgroup that stays for several tiles, all
+// weights in registers, two to a compute unit, took 46.1.
+constexpr int XF = 18;        // FP32 input pixels per side for the bilinear skip of a tile
+constexpr int ISTRIDE = 32;   // BF16 elements per pixel of the hidden activations: with 64 bytes the kernel takes
+                               // 51 KB of LDS, so that three workgroups fit a compute unit
+__global__ __launch_bounds__(256, 3) void infer_kernel(CnnInferArgs a) {
   __shared__ __attribute__((aligned(16))) float xbuf[XF * XF * 4];   // BF16 22x22x4 input, then FP32 18x18x4
-  __shared__ __attribute__((aligned(16))) uint16_t a1[20 * 20 * PSTRIDE];
-  __shared__ __attribute__((aligned(16))) uint16_t a2[18 * 18 * PSTRIDE];
+  __shared__ __attribute__((aligned(16))) uint16_t a1[20 * 20 * ISTRIDE];
+  __shared__ __attribute__((aligned(16))) uint16_t a2[18 * 18 * ISTRIDE];
   static_assert(sizeof(uint16_t) * 22 * 22 * 4 <= sizeof(float) * XF * XF * 4, "input tile fits");
-  static_assert(sizeof(uint16_t) * 20 * 20 * PSTRIDE >= sizeof(float) * 32 * 32 * 4, "output tile fits");
+  static_assert(sizeof(a1) >= sizeof(float) * 32 * 32 * 4, "output tile fits");
   uint16_t* xs = reinterpret_cast<uint16_t*>(xbuf);
   const int H = a.h, W = a.w;
   const int n = blockIdx.z;
   const int oy = blockIdx.y * 16, ox = blockIdx.x * 16;
-  const float* __restrict__ x = a.x + (int64_t)n * H * W * 4;
+  const float4* __restrict__ x = reinterpret_cast<const float4*>(a.x) + (int64_t)n * H * W;
   float* __restrict__ out = a.out + (int64_t)n * 4 * H * W * 4;
+  const int tid = threadIdx.x, g = (tid & 63) >> 4;
+  float4 in[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int i = tid + 256 * k, gy = oy - 3 + i / 22, gx = ox - 3 + i % 22;
+    in[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i < 22 * 22 && gy >= 0 && gy < H && gx >= 0 && gx < W) in[k] = x[(int64_t)gy * W + gx];
+  }
+  bf16x8 w1[4], w2[18];
+  load_weights(a.wf1, w1);
   const float* __restrict__ bias = a.params;
-  for (int i = threadIdx.x; i < 22 * 22; i += blockDim.x) {
-    const int gy = oy - 3 + i / 22, gx = ox - 3 + i % 22;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (gy >= 0 && gy < H && gx >= 0 && gx < W) v = reinterpret_cast<const float4*>(x)[(int64_t)gy * W + gx];
-    xs[i * 4 + 0] = bf16_bits(v.x);
-    xs[i * 4 + 1] = bf16_bits(v.y);
-    xs[i * 4 + 2] = bf16_bits(v.z);
-    xs[i * 4 + 3] = bf16_bits(v.w);
+  float bv[2][4];
+  auto biases = [&](int at, int nt_count) {
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (nt < nt_count) bv[nt][i] = bias[at + 16 * nt + 4 * g + i];
+  };
+  biases(CNN_OFF_B1, 2);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int i = tid + 256 * k;
+    if (i < 22 * 22) *reinterpret_cast<uint2*>(xs + 4 * i) = bf16_pack(in[k].x, in[k].y, in[k].z, in[k].w);
   }
   __syncthreads();
-  const int r16 = threadIdx.x & 15;
-  const float b1a = bias[CNN_OFF_B1 + r16], b1b = bias[CNN_OFF_B1 + 16 + r16];
-  conv_tile<4, 2, 2, 4, 22, 4, 400, 20>(xs, a.wf1, [&](int p0, const f32x4* v) {
+  load_weights(a.wf2, w2);
+  // a hidden layer's outputs are zero outside the image (the next one's padding)
+  const bool inner = oy >= 2 && ox >= 2 && oy + 18 <= H && ox + 18 <= W;
+  auto hidden = [&](uint16_t* d, int y, int z, const f32x4* v) {
+    const bool keep = inner || (y >= 0 && y < H && z >= 0 && z < W);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int p = p0 + i;
-      if (p >= 400) break;
-      const int gy = oy - 2 + p / 20, gx = ox - 2 + p % 20;
-      const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
-      uint16_t* d = a1 + p * PSTRIDE + r16;
-      d[0] = in ? bf16_bits(fmaxf(v[0][i] + b1a, 0.0f)) : (uint16_t)0;
-      d[16] = in ? bf16_bits(fmaxf(v[1][i] + b1b, 0.0f)) : (uint16_t)0;
+    for (int nt = 0; nt < 2; ++nt) {
+      float q[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) q[i] = fmaxf(v[nt][i] + bv[nt][i], 0.0f);
+      const uint2 u = bf16_pack(q[0], q[1], q[2], q[3]);
+      *reinterpret_cast<uint2*>(d + 16 * nt + 4 * g) = make_uint2(keep ? u.x : 0u, keep ? u.y : 0u);
     }
+  };
+  conv_tile<4, 2, 2, 4, 22, 4, 400, 20>(xs, w1, [&](int p, const f32x4* v) {
+    hidden(a1 + p * ISTRIDE, oy - 2 + p / 20, ox - 2 + p % 20, v);
   });
+  biases(CNN_OFF_B2, 2);
   __syncthreads();
   // FP32 input rows oy-1 .. oy+16 and columns ox-1 .. ox+16, clamped to the
   // image as the bilinear skip clamps them
-  for (int i = threadIdx.x; i < XF * XF; i += blockDim.x) {
+  for (int i = tid; i < XF * XF; i += 256) {
     const int gy = min(max(oy - 1 + i / XF, 0), H - 1), gx = min(max(ox - 1 + i % XF, 0), W - 1);
-    reinterpret_cast<float4*>(xbuf)[i] = reinterpret_cast<const float4*>(x)[(int64_t)gy * W + gx];
+    reinterpret_cast<float4*>(xbuf)[i] = x[(int64_t)gy * W + gx];
   }
-  const float b2a = bias[CNN_OFF_B2 + r16], b2b = bias[CNN_OFF_B2 + 16 + r16];
-  conv_tile<32, 9, 2, 3, 20, PSTRIDE, 324, 18>(a1, a.wf2, [&](int p0, const f32x4* v) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int p = p0 + i;
-      if (p >= 324) break;
-      const int gy = oy - 1 + p / 18, gx = ox - 1 + p % 18;
-      const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
-      uint16_t* d = a2 + p * PSTRIDE + r16;
-      d[0] = in ? bf16_bits(fmaxf(v[0][i] + b2a, 0.0f)) : (uint16_t)0;
-      d[16] = in ? bf16_bits(fmaxf(v[1][i] + b2b, 0.0f)) : (uint16_t)0;
-    }
+  conv_tile<32, 9, 2, 2, 20, ISTRIDE, 324, 18>(a1, w2, [&](int p, const f32x4* v) {
+    hidden(a2 + p * ISTRIDE, oy - 1 + p / 18, ox - 1 + p % 18, v);
   });
+  bf16x8 w3[9];
+  load_weights(a.wf3, w3);
+  biases(CNN_OFF_B3, 1);
   __syncthreads();
   float* ot = reinterpret_cast<float*>(a1);   // [32][32] fine pixels x 4 channels
-  // the lane's output channel 4c + 2dy + dx goes to fine pixel (2i + dy, 2j + dx), channel c
-  const float b3v = bias[CNN_OFF_B3 + r16];
-  const int c3 = r16 >> 2, dy3 = (r16 >> 1) & 1, dx3 = r16 & 1;
-  conv_tile<32, 9, 1, 4, 18, PSTRIDE, 256, 16>(a2, a.wf3, [&](int p0, const f32x4* v) {
-    // p0 .. p0+3 lie in one row of the 16-pixel-wide tile
-    float* d = ot + ((2 * (p0 / 16) + dy3) * 32 + 2 * (p0 % 16) + dx3) * 4 + c3;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) d[8 * i] = v[0][i] + b3v;
+  // channel 4c + 2dy + dx goes to fine pixel (2i + dy, 2j + dx), channel c: the lane's four are c = g
+  conv_tile<32, 9, 1, 4, 18, ISTRIDE, 256, 16>(a2, w3, [&](int p, const f32x4* v) {
+    float* d = ot + ((2 * (p >> 4)) * 32 + 2 * (p & 15)) * 4 + g;
+    d[0] = v[0][0] + bv[0][0];
+    d[4] = v[0][1] + bv[0][1];
+    d[128] = v[0][2] + bv[0][2];
+    d[132] = v[0][3] + bv[0][3];
   });
   __syncthreads();
   // out = shuffled network output + bilinear x2 of x (half-pixel centres,
-  // clamp to edge), whole fine pixels per thread
-  for (int i = threadIdx.x; i < 32 * 32; i += blockDim.x) {
-    const int fy = i / 32, fx = i % 32;
+  // clamp to edge), whole fine pixels per thread; fine coordinates lie a
+  // quarter to either side of the coarse one (xbuf holds the clamped
+  // neighbours)
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int i = tid + 256 * k, fy = i / 32, fx = i % 32;
     const int Y = 2 * oy + fy, X = 2 * ox + fx;
-    if (Y >= 2 * H || X >= 2 * W) continue;
-    const float cy = ((float)Y + 0.5f) * 0.5f - 0.5f, cx = ((float)X + 0.5f) * 0.5f - 0.5f;
-    const float fy0 = floorf(cy), fx0 = floorf(cx);
-    const float ty = cy - fy0, tx = cx - fx0;
-    const int y0 = min(max((int)fy0, 0), H - 1) - (oy - 1), y1 = min(max((int)fy0 + 1, 0), H - 1) - (oy - 1);
-    const int x0 = min(max((int)fx0, 0), W - 1) - (ox - 1), x1 = min(max((int)fx0 + 1, 0), W - 1) - (ox - 1);
-    const float4 v00 = reinterpret_cast<const float4*>(xbuf)[y0 * XF + x0];
-    const float4 v01 = reinterpret_cast<const float4*>(xbuf)[y0 * XF + x1];
-    const float4 v10 = reinterpret_cast<const float4*>(xbuf)[y1 * XF + x0];
-    const float4 v11 = reinterpret_cast<const float4*>(xbuf)[y1 * XF + x1];
+    const float ty = (fy & 1) ? 0.25f : 0.75f, tx = (fx & 1) ? 0.25f : 0.75f;
+    const int at = ((fy + 1) >> 1) * XF + ((fx + 1) >> 1);
+    const float4* xv = reinterpret_cast<const float4*>(xbuf) + at;
+    const float4 v00 = xv[0], v01 = xv[1], v10 = xv[XF], v11 = xv[XF + 1];
     const float4 z = reinterpret_cast<const float4*>(ot)[i];
     auto bl = [&](float a00, float a01, float a10, float a11) {
       const float top = a00 * (1.0f - tx) + a01 * tx;
@@ -264,7 +274,7 @@ __global__ __launch_bounds__(256) void infer_kernel(CnnInferArgs a) {
     o.y = z.y + bl(v00.y, v01.y, v10.y, v11.y);
     o.z = z.z + bl(v00.z, v01.z, v10.z, v11.z);
     o.w = z.w + bl(v00.w, v01.w, v10.w, v11.w);
-    reinterpret_cast<float4*>(out)[(int64_t)Y * 2 * W + X] = o;
+    if (Y < 2 * H && X < 2 * W) reinterpret_cast<float4*>(out)[(int64_t)Y * 2 * W + X] = o;
   }
 }
 
@@ -292,6 +302,9 @@ __device__ void stage_tile(uint16_t* t, int sin, const float* __restrict__ img, 
   }
 }
 
+// At 960x540: forward 14.4, 22.4 and (with the loss) 32.8 us, backward 17.7 and
+// 26 us; 14.6, 24, 37.6, 28.6 and 33 with a lane's results in one channel of
+// four pixels (2-byte stores, 4-byte loads of the target).
 // mode 0: a = bf16(relu(z + b)) stored NHWC (COUT channels)
 // mode 1: g = bf16(z * [mask > 0]) stored NHWC (backward-data with ReLU mask)
 // mode 2: last layer + loss: y = z + b, out = shuffle(y) + bilinear(x),
@@ -299,51 +312,99 @@ __device__ void stage_tile(uint16_t* t, int sin, const float* __restrict__ img, 
 template <int CIN, int COUT, int KS, int MODE>
 __global__ __launch_bounds__(256) void layer_kernel(CnnLayerArgs a) {
   constexpr int SIN = CIN == 4 ? 4 : PSTRIDE;
+  constexpr int NT = COUT / 16;
   __shared__ __attribute__((aligned(16))) uint16_t t[18 * 18 * SIN];
-  __shared__ float red[256];
+  // last layer: its outputs as fine pixels, the image around them, and their gradients
+  __shared__ float4 ot[MODE == 2 ? 32 * 32 : 1], xi[MODE == 2 ? 18 * 18 : 1];
+  __shared__ __attribute__((aligned(16))) uint16_t gt[MODE == 2 ? 256 * 16 : 8];
+  __shared__ float red[MODE == 2 ? 256 : 1];
   const int H = a.h, W = a.w;
   const int n = blockIdx.z;
   const int oy = blockIdx.y * 16, ox = blockIdx.x * 16;
   const int64_t plane = (int64_t)H * W;
+  bf16x8 w[KS * NT];
+  load_weights(a.wf, w);
   stage_tile<CIN>(t, SIN, a.img ? a.img + n * plane * 4 : nullptr, a.in ? a.in + n * plane * CIN : nullptr, H, W, oy, ox);
+  if (MODE == 2)
+    for (int i = threadIdx.x; i < 18 * 18; i += 256) {
+      const int gy = min(max(oy - 1 + i / 18, 0), H - 1), gx = min(max(ox - 1 + i % 18, 0), W - 1);
+      xi[i] = reinterpret_cast<const float4*>(a.img)[n * plane + (int64_t)gy * W + gx];
+    }
+  const int g = (threadIdx.x & 63) >> 4;
+  float bv[NT][4];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bv[nt][i] = MODE == 1 ? 0.0f : a.bias[16 * nt + 4 * g + i];
   __syncthreads();
-  float sq = 0.0f;
-  constexpr int NT = COUT / 16;
-  const int r16 = threadIdx.x & 15;
-  float bv[NT];
+  conv_tile<CIN, KS, NT, 4, 18, SIN, 256, 16>(t, w, [&](int p, const f32x4* v) {
+    if (MODE == 2) {
+      // channel 4c + 2dy + dx is channel c of fine pixel (2 gy + dy, 2 gx + dx): the lane's four are c = g
+      float* d = reinterpret_cast<float*>(ot) + ((2 * (p >> 4)) * 32 + 2 * (p & 15)) * 4 + g;
+      d[0] = v[0][0] + bv[0][0];
+      d[4] = v[0][1] + bv[0][1];
+      d[128] = v[0][2] + bv[0][2];
+      d[132] = v[0][3] + bv[0][3];
+      return;
+    }
+    const int gy = oy + p / 16, gx = ox + p % 16;
+    if (gy >= H || gx >= W) return;
+    const int64_t pix = n * plane + (int64_t)gy * W + gx;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) bv[nt] = MODE == 1 ? 0.0f : a.bias[16 * nt + r16];
-  conv_tile<CIN, KS, NT, 4, 18, SIN, 256, 16>(t, a.wf, [&](int p0, const f32x4* v) {
+    for (int nt = 0; nt < NT; ++nt) {
+      // four consecutive channels of one pixel: 8-byte loads and stores
+      const int64_t at = pix * COUT + 16 * nt + 4 * g;
+      uint2* out = reinterpret_cast<uint2*>(a.out + at);
+      if (MODE == 0) {
+        float z[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int p = p0 + i;
-      const int gy = oy + p / 16, gx = ox + p % 16;
-      if (gy >= H || gx >= W) continue;
-      const int64_t pix = n * plane + (int64_t)gy * W + gx;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int c = 16 * nt + r16;
-        const float z = v[nt][i];
-        if (MODE == 0) {
-          a.out[pix * COUT + c] = bf16_bits(fmaxf(z + bv[nt], 0.0f));
-        } else if (MODE == 1) {
-          a.out[pix * COUT + c] = (a.mask[pix * COUT + c] & 0x7fffu) != 0 ? bf16_bits(z) : (uint16_t)0;
-        } else {
-          const float* xi = a.img + n * plane * 4;
-          const int ch = c >> 2, dy = (c >> 1) & 1, dx = c & 1;
-          const int Y = 2 * gy + dy, X = 2 * gx + dx;
-          const int64_t fi = ((int64_t)n * 4 * plane + (int64_t)Y * 2 * W + X) * 4 + ch;
-          const float o = (z + bv[nt]) + bilinear2(xi, H, W, Y, X, ch);
-          const float d = o - a.target[fi];
-          sq += d * d;
-          a.out[pix * COUT + c] = bf16_bits(d * a.grad_scale);
-        }
+        for (int i = 0; i < 4; ++i) z[i] = fmaxf(v[nt][i] + bv[nt][i], 0.0f);
+        *out = bf16_pack(z[0], z[1], z[2], z[3]);
+      } else if (MODE == 1) {
+        const uint2 m = *reinterpret_cast<const uint2*>(a.mask + at);
+        *out = bf16_pack((m.x & 0x7fffu) ? v[nt][0] : 0.0f, (m.x & 0x7fff0000u) ? v[nt][1] : 0.0f,
+                         (m.y & 0x7fffu) ? v[nt][2] : 0.0f, (m.y & 0x7fff0000u) ? v[nt][3] : 0.0f);
       }
     }
   });
   if (MODE == 2) {
+    // whole fine pixels per thread, so that the target is read and the
+    // gradient written in whole lines
+    float sq = 0.0f;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int i = threadIdx.x + 256 * k, fy = i / 32, fx = i % 32, Y = 2 * oy + fy, X = 2 * ox + fx;
+      // bilinear x2 (half-pixel centres, clamp to edge): fine coordinates lie
+      // a quarter to either side of the coarse one
+      const float ty = (fy & 1) ? 0.25f : 0.75f, tx = (fx & 1) ? 0.25f : 0.75f;
+      const float4* xv = xi + ((fy + 1) >> 1) * 18 + ((fx + 1) >> 1);
+      const float4 v00 = xv[0], v01 = xv[1], v10 = xv[18], v11 = xv[19], z = ot[i];
+      const bool in = Y < 2 * H && X < 2 * W;
+      float4 tg = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (in) tg = reinterpret_cast<const float4*>(a.target)[n * 4 * plane + (int64_t)Y * 2 * W + X];
+      auto diff = [&](float zc, float a00, float a01, float a10, float a11, float t) {
+        const float top = a00 * (1.0f - tx) + a01 * tx;
+        const float bot = a10 * (1.0f - tx) + a11 * tx;
+        return (zc + (top * (1.0f - ty) + bot * ty)) - t;
+      };
+      const float d[4] = {diff(z.x, v00.x, v01.x, v10.x, v11.x, tg.x), diff(z.y, v00.y, v01.y, v10.y, v11.y, tg.y),
+                          diff(z.z, v00.z, v01.z, v10.z, v11.z, tg.z), diff(z.w, v00.w, v01.w, v10.w, v11.w, tg.w)};
+      // channel 4c + 2dy + dx of the coarse pixel is channel c of fine pixel (dy, dx)
+      uint16_t* gp = gt + ((fy >> 1) * 16 + (fx >> 1)) * 16 + 2 * (fy & 1) + (fx & 1);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if (in) sq += d[c] * d[c];
+        gp[4 * c] = bf16_bits(d[c] * a.grad_scale);
+      }
+    }
     red[threadIdx.x] = sq;
     __syncthreads();
+    for (int i = threadIdx.x; i < 512; i += 256) {
+      const int gy = oy + i / 32, gx = ox + (i >> 1) % 16;
+      if (gy < H && gx < W)
+        reinterpret_cast<uint4*>(a.out + (n * plane + (int64_t)gy * W + gx) * 16)[i & 1] = reinterpret_cast<const uint4*>(gt)[i];
+    }
     for (int s = 128; s > 0; s >>= 1) {
       if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
       __syncthreads();
@@ -363,10 +424,11 @@ __global__ __launch_bounds__(256) void layer_kernel(CnnLayerArgs a) {
 // (the tap one to the right is the same bytes shifted by one pixel).  A
 // workgroup keeps its sums in the accumulators over all its tiles
 // (blockIdx.x, + gridDim.x, ...) and writes one partial vector at its end, in
-// the layout of the parameters.  At 960x540 the three launches take 34, 45 and
-// 25 us and the reduction of all layers with the update 11 us; one partial
-// vector per tile, gathered element by element from LDS, took 46, 85 and 37
-// us, and 473 us for each layer's reduction (one thread per parameter).
+// the layout of the parameters; the next tile's inputs come to registers during
+// a tile.  At 960x540 the three launches take 18, 25 and 11 us and the reduction
+// of all layers with the update 11 us; without the loads ahead 34, 45 and 25;
+// with one partial vector per tile, gathered element by element from LDS, 46,
+// 85 and 37, and 473 us for each layer's reduction (one thread per parameter).
 constexpr int XROW = 24;               // elements per staged row of x: 18 pixels, rows 16-byte aligned
 constexpr int XCH = 18 * XROW + 8;     // elements per staged channel of x and of g: the 16 channels that
 constexpr int GCH = 256 + 8;           // a read touches start 4 banks apart, so their 16 bytes cover all banks once
@@ -401,46 +463,65 @@ __global__ __launch_bounds__(256) void wgrad_kernel(CnnWgradArgs a) {
 #pragma unroll
   for (int j = 0; j < NB; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const bf16x8 ones = as_bf16x8(make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
+  // the thread's share of a tile, on its way while the tile before is summed:
+  // 18 rows of nine pixel pairs of x (zero outside the image), 128 pairs of g
+  constexpr int XQ = IMG ? 1 : CIN / 8, XN = (162 * XQ + 255) / 256, GQ = COUT / 8, GN = 128 * GQ / 256;
+  uint4 xr[XN][2], gr[GN][2];
+  float4 fr[2];
+  auto fetch = [&](int tile) {
+    const int n = tile / (tx * ty), rem = tile - n * (tx * ty), oy = (rem / tx) * 16, ox = (rem % tx) * 16;
+    const uint4 z = make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < XN; ++t) {
+      const int i = tid + 256 * t, q = i % XQ, pr = i / XQ, row = pr / 9, k = pr % 9;
+      const int gy = oy - 1 + row, gx = ox - 1 + 2 * k;
+      const bool in = i < 162 * XQ && gy >= 0 && gy < H, in0 = in && gx >= 0 && gx < W, in1 = in && gx + 1 < W;
+      const int64_t pix = n * plane + (int64_t)gy * W + gx;
+      if constexpr (IMG) {
+        fr[0] = fr[1] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (in0) fr[0] = reinterpret_cast<const float4*>(a.img)[pix];
+        if (in1) fr[1] = reinterpret_cast<const float4*>(a.img)[pix + 1];
+      } else {
+        xr[t][0] = xr[t][1] = z;
+        if (in0) xr[t][0] = reinterpret_cast<const uint4*>(a.x + pix * CIN)[q];
+        if (in1) xr[t][1] = reinterpret_cast<const uint4*>(a.x + (pix + 1) * CIN)[q];
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < GN; ++t) {
+      const int i = tid + 256 * t, q = i % GQ, pr = i / GQ, gy = oy + (pr >> 3), gx = ox + 2 * (pr & 7);
+      const int64_t pix = n * plane + (int64_t)gy * W + gx;
+      gr[t][0] = gr[t][1] = z;
+      if (gy < H && gx < W) gr[t][0] = reinterpret_cast<const uint4*>(a.g + pix * COUT)[q];
+      if (gy < H && gx + 1 < W) gr[t][1] = reinterpret_cast<const uint4*>(a.g + (pix + 1) * COUT)[q];
+    }
+  };
+  fetch(blockIdx.x);
   for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
-    const int n = tile / (tx * ty), rem = tile - n * (tx * ty);
-    const int oy = (rem / tx) * 16, ox = (rem % tx) * 16;
     __syncthreads();   // the tile before has been read
     uint32_t* xp = reinterpret_cast<uint32_t*>(xt);
     uint32_t* gp = reinterpret_cast<uint32_t*>(gt);
-    // x: 18 rows of nine pixel pairs, zero outside the image
-    constexpr int XQ = IMG ? 1 : CIN / 8;
-    for (int i = tid; i < 162 * XQ; i += 256) {
-      const int q = i % XQ, pr = i / XQ, row = pr / 9, k = pr % 9;
-      const int gy = oy - 1 + row, gx = ox - 1 + 2 * k;
-      const bool in0 = gy >= 0 && gy < H && gx >= 0 && gx < W, in1 = gy >= 0 && gy < H && gx + 1 >= 0 && gx + 1 < W;
-      const int64_t pix = n * plane + (int64_t)gy * W + gx;
-      uint32_t* d = xp + (8 * q) * (XCH / 2) + row * (XROW / 2) + k;
+#pragma unroll
+    for (int t = 0; t < XN; ++t) {
+      const int i = tid + 256 * t, q = i % XQ, pr = i / XQ;
+      if (i >= 162 * XQ) break;
+      uint32_t* d = xp + (8 * q) * (XCH / 2) + (pr / 9) * (XROW / 2) + pr % 9;
       if constexpr (IMG) {
-        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-        const float4 u = in0 ? reinterpret_cast<const float4*>(a.img)[pix] : z;
-        const float4 v = in1 ? reinterpret_cast<const float4*>(a.img)[pix + 1] : z;
-        d[0] = bf16_bits(u.x) | (uint32_t)bf16_bits(v.x) << 16;
-        d[XCH / 2] = bf16_bits(u.y) | (uint32_t)bf16_bits(v.y) << 16;
-        d[XCH] = bf16_bits(u.z) | (uint32_t)bf16_bits(v.z) << 16;
-        d[3 * (XCH / 2)] = bf16_bits(u.w) | (uint32_t)bf16_bits(v.w) << 16;
+        d[0] = bf16_bits(fr[0].x) | (uint32_t)bf16_bits(fr[1].x) << 16;
+        d[XCH / 2] = bf16_bits(fr[0].y) | (uint32_t)bf16_bits(fr[1].y) << 16;
+        d[XCH] = bf16_bits(fr[0].z) | (uint32_t)bf16_bits(fr[1].z) << 16;
+        d[3 * (XCH / 2)] = bf16_bits(fr[0].w) | (uint32_t)bf16_bits(fr[1].w) << 16;
       } else {
-        const uint4 z = make_uint4(0, 0, 0, 0);
-        const uint4 u = in0 ? reinterpret_cast<const uint4*>(a.x + pix * CIN)[q] : z;
-        const uint4 v = in1 ? reinterpret_cast<const uint4*>(a.x + (pix + 1) * CIN)[q] : z;
-        store_pairs(d, XCH / 2, u, v);
+        store_pairs(d, XCH / 2, xr[t][0], xr[t][1]);
       }
     }
-    constexpr int GQ = COUT / 8;
-    for (int i = tid; i < 128 * GQ; i += 256) {
-      const int q = i % GQ, pr = i / GQ, row = pr >> 3, k = pr & 7;
-      const int gy = oy + row, gx = ox + 2 * k;
-      const int64_t pix = n * plane + (int64_t)gy * W + gx;
-      const uint4 z = make_uint4(0, 0, 0, 0);
-      const uint4 u = gy < H && gx < W ? reinterpret_cast<const uint4*>(a.g + pix * COUT)[q] : z;
-      const uint4 v = gy < H && gx + 1 < W ? reinterpret_cast<const uint4*>(a.g + (pix + 1) * COUT)[q] : z;
-      store_pairs(gp + (8 * q) * (GCH / 2) + pr, GCH / 2, u, v);
+#pragma unroll
+    for (int t = 0; t < GN; ++t) {
+      const int i = tid + 256 * t, q = i % GQ, pr = i / GQ;
+      store_pairs(gp + (8 * q) * (GCH / 2) + pr, GCH / 2, gr[t][0], gr[t][1]);
     }
     __syncthreads();
+    if (tile + (int)gridDim.x < a.n_tiles) fetch(tile + gridDim.x);
 #pragma unroll
     for (int s = 0; s < 8 / KH; ++s) {
       const int row = 2 * (s + (8 / KH) * kh) + (g >> 1), xo = 8 * (g & 1);
