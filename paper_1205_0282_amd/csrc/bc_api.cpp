@@ -1060,8 +1060,8 @@ int render_impl(bc_ctx* c, float* out, void* stream, float4* sub, int64_t sub_ca
         HIPCHECK(c, bc_launch_render(fv, c->render_workgroups, s));
         HIPCHECK(c, bc_launch_composite(fv, reinterpret_cast<float4*>(val_img), s));
       }
-      // the decision is written to the first set of counters, which the
-      // conditional pass reads
+      // the shares go to the first set of counters, from which the conditional
+      // pass's set-up decides
       HIPCHECK(c, bc_launch_psnr(fv, reinterpret_cast<const float4*>(val_img), reinterpret_cast<const float4*>(out), s));
       BcFramePtrs fp = pass_ptrs(c, f, 2, W, H);
       HIPCHECK(c, bc_launch_setup(fp, s));

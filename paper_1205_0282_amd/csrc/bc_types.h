@@ -91,6 +91,7 @@ struct BcQueueCounter {
   uint32_t pad_[31];
 };
 #define BC_COUNT_PARTS 16
+#define BC_PSNR_PARTS 64   // one per lane of the wave that adds them up
 struct BcCountPart {
   unsigned long long count[2];   // nominal, evaluated
   uint32_t pad_[28];
@@ -109,6 +110,8 @@ struct BcCounters {
   unsigned long long evaluated;
   uint32_t pad1_[28];
   BcQueueCounter q[8];
+  float psnr_sum[BC_PSNR_PARTS];       // learned frame: squared differences of the validation tiles,
+  int32_t psnr_count[BC_PSNR_PARTS];   // and their number, a share per workgroup
   BcCountPart part[BC_COUNT_PARTS];    // further shares of the sample counts (launches of a workgroup per item)
   uint32_t minmax[BC_MAX_BRICKS][2];   // load time: ordered-int min/max per brick
 };
