@@ -28,7 +28,7 @@ def flags() -> list:
         "-fhip-fp32-correctly-rounded-divide-sqrt",
         # no packed FP32 instructions in the device code
         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-        "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
+        "-pthread", "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
         "-I", os.path.join(HERE, "..", "include"),
     ]
 

@@ -6,13 +6,16 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <map>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/brickcast.h"
@@ -117,9 +120,10 @@ struct bc_ctx {
   hipEvent_t frame_done = nullptr;   // the last frame's slot event
   bool frame_pending = false;
   int frame_views = 0;
-  // host-source load staging (pinned)
-  void* load_staging = nullptr;
-  size_t load_staging_bytes = 0;
+  // host-source load staging (pinned): one brick's region is gathered while
+  // the one before is on its way to the device
+  void* load_staging[2] = {nullptr, nullptr};
+  hipEvent_t load_copied[2] = {nullptr, nullptr};
   // transfer function and views (host copies)
   std::vector<float> tf;
   int K = 0;
@@ -468,6 +472,162 @@ CnnLayout cnn_layout(int n, int h, int w) {
 
 int cnn_infer(bc_ctx* c, const CnnLayout& L, const float* coarse, float* fine, int n, int h, int w, hipStream_t st);
 
+// Threads that gather a host source's bricks into the staging buffers, each
+// brick in `kParts` runs of rows.  Brick b goes to buffer b % 2 and is taken up
+// once release() has let it.
+class Gather {
+ public:
+  static constexpr int kParts = 16;
+  struct Brick {
+    const char* src;               // first element of the region
+    int64_t row, plane, elem;      // byte strides of the source
+    int64_t rx, ry, rz, bytes;     // region, bytes per element
+  };
+
+  Gather(std::vector<Brick> bricks, void* const* buffers, int threads) : bricks_(std::move(bricks)), left_(bricks_.size(), kParts) {
+    buffer_[0] = static_cast<char*>(buffers[0]);
+    buffer_[1] = static_cast<char*>(buffers[1]);
+    try {
+      for (int i = 0; i < threads; ++i) threads_.emplace_back([this] { work(); });
+    } catch (...) {   // (as many as there are; wait() does the work where there are none)
+    }
+  }
+  ~Gather() {
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      stop_ = true;
+    }
+    cv_.notify_all();
+    for (std::thread& t : threads_) t.join();
+  }
+  // bricks below n may be gathered
+  void release(int n) {
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      released_ = n;
+    }
+    cv_.notify_all();
+  }
+  // until brick b is in its buffer
+  void wait(int b) {
+    if (threads_.empty()) {
+      for (int k = 0; k < kParts; ++k) part(b, k);
+      return;
+    }
+    std::unique_lock<std::mutex> lock(mu_);
+    cv_.wait(lock, [&] { return left_[b] == 0; });
+  }
+
+ private:
+  void part(int b, int k) {
+    const Brick& g = bricks_[b];
+    const int64_t rows = g.ry * g.rz, n = g.rx * g.bytes;
+    char* out = buffer_[b & 1] + rows * k / kParts * n;
+    for (int64_t r = rows * k / kParts; r < rows * (k + 1) / kParts; ++r, out += n) {
+      const char* in = g.src + (r / g.ry) * g.plane + (r % g.ry) * g.row;
+      if (g.elem == g.bytes) std::memcpy(out, in, (size_t)n);
+      else
+        for (int64_t x = 0; x < g.rx; ++x) std::memcpy(out + x * g.bytes, in + x * g.elem, (size_t)g.bytes);
+    }
+  }
+  void work() {
+    const int64_t total = (int64_t)bricks_.size() * kParts;
+    for (;;) {
+      const int64_t t = next_.fetch_add(1);
+      if (t >= total) return;
+      const int b = (int)(t / kParts);
+      {
+        std::unique_lock<std::mutex> lock(mu_);
+        cv_.wait(lock, [&] { return stop_ || b < released_; });
+        if (stop_) return;
+      }
+      part(b, (int)(t % kParts));
+      std::lock_guard<std::mutex> lock(mu_);
+      if (--left_[b] == 0) cv_.notify_all();
+    }
+  }
+  std::vector<Brick> bricks_;
+  std::vector<int> left_;          // parts of each brick still to do
+  char* buffer_[2];
+  std::vector<std::thread> threads_;
+  std::mutex mu_;
+  std::condition_variable cv_;
+  std::atomic<int64_t> next_{0};
+  int released_ = 0;
+  bool stop_ = false;
+};
+
+// Bricks of a host source: each one's ghosted region (clamped to the cube) is
+// gathered into pinned staging, copied into the scratch region and converted,
+// the next one being gathered meanwhile.  One thread's row copies (12 GB/s,
+// one brick after the other: 8.5 ms for a 301x257x323 FP32 cube) held all of
+// it up; with eight 3.6 ms.
+template <typename Convert>
+int load_from_host(bc_ctx* c, const void* src, const int64_t* strides, const int64_t* box_lo, hipStream_t st,
+                   const Convert& convert) {
+  const bc_volume_desc& d = c->desc;
+  const int64_t eb = (int64_t)c->src_elem_bytes;
+  std::vector<Gather::Brick> bricks;
+  std::vector<BcLoadSrc> from;
+  int64_t all = 0;
+  for (const BcBrick& hb : c->bricks) {
+    int64_t lo[3], n[3];
+    for (int a = 0; a < 3; ++a) {
+      lo[a] = std::max<int64_t>(hb.lo[a] - 1, 0);
+      n[a] = std::min<int64_t>(hb.hi[a] + 1, d.global_dims[a]) - lo[a];
+    }
+    Gather::Brick g;
+    g.src = static_cast<const char*>(src) +
+            ((lo[2] - box_lo[2]) * strides[2] + (lo[1] - box_lo[1]) * strides[1] + (lo[0] - box_lo[0]) * strides[0]) * eb;
+    g.elem = strides[0] * eb;
+    g.row = strides[1] * eb;
+    g.plane = strides[2] * eb;
+    g.rx = n[0];
+    g.ry = n[1];
+    g.rz = n[2];
+    g.bytes = eb;
+    const int64_t need = n[0] * n[1] * n[2] * eb;
+    if ((size_t)need > c->bytes[3]) return fail(c, BC_E_NOMEM, "bc_load_bricks: scratch region too small");
+    all += need;
+    BcLoadSrc s;
+    s.dtype = d.src_dtype == BC_F32 ? 0 : 1;
+    s.ptr = c->dev[3];
+    s.strides[0] = 1;
+    s.strides[1] = n[0];
+    s.strides[2] = n[0] * n[1];
+    for (int a = 0; a < 3; ++a) {
+      s.dims[a] = (int32_t)d.global_dims[a];
+      s.origin[a] = (int32_t)lo[a];
+    }
+    bricks.push_back(g);
+    from.push_back(s);
+  }
+  for (int i = 0; i < 2; ++i) {
+    if (!c->load_staging[i]) HIPCHECK(c, hipHostMalloc(&c->load_staging[i], c->bytes[3], hipHostMallocDefault));
+    if (!c->load_copied[i]) HIPCHECK(c, hipEventCreateWithFlags(&c->load_copied[i], hipEventDisableTiming));
+  }
+  // (a thread to start costs about what it copies of 256 KB)
+  const int threads = all < (int64_t(2) << 20) ? 0
+                      : (int)std::min<int64_t>({8, all >> 20, std::max<int64_t>(std::thread::hardware_concurrency(), 1)});
+  const int n = (int)bricks.size();
+  Gather gather(std::move(bricks), c->load_staging, threads);
+  gather.release(std::min(n, 2));
+  for (int b = 0; b < n; ++b) {
+    gather.wait(b);
+    const BcLoadSrc& s = from[b];
+    const size_t bytes = (size_t)(s.strides[2] * (std::min<int64_t>(c->bricks[b].hi[2] + 1, d.global_dims[2]) - s.origin[2]) * eb);
+    HIPCHECK(c, hipMemcpyAsync(c->dev[3], c->load_staging[b & 1], bytes, hipMemcpyHostToDevice, st));
+    HIPCHECK(c, hipEventRecord(c->load_copied[b & 1], st));
+    HIPCHECK(c, convert(s, b, 1));
+    // the buffer of the brick after next
+    if (b + 2 < n) {
+      HIPCHECK(c, hipEventSynchronize(c->load_copied[b & 1]));
+      gather.release(b + 3);
+    }
+  }
+  return BC_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -543,7 +703,10 @@ void bc_destroy(bc_ctx* c) {
     if (c->aux_stream) (void)hipStreamDestroy(c->aux_stream);
     if (c->fork_ev) (void)hipEventDestroy(c->fork_ev);
     if (c->join_ev) (void)hipEventDestroy(c->join_ev);
-    if (c->load_staging) (void)hipHostFree(c->load_staging);
+    for (int i = 0; i < 2; ++i) {
+      if (c->load_staging[i]) (void)hipHostFree(c->load_staging[i]);
+      if (c->load_copied[i]) (void)hipEventDestroy(c->load_copied[i]);
+    }
   }
   delete c;
 }
@@ -760,51 +923,9 @@ int bc_load_bricks(bc_ctx* c, const void* src, const int64_t strides[3], int src
     HIPCHECK(c, convert(s, 0, c->n_bricks));
   }
   // a host source goes through the load scratch region one brick at a time
-  for (int b = 0; b < c->n_bricks && !src_on_device; ++b) {
-    const BcBrick& hb = c->bricks[b];
-    BcLoadSrc s;
-    s.dtype = d.src_dtype == BC_F32 ? 0 : 1;
-    for (int a = 0; a < 3; ++a) s.dims[a] = (int32_t)d.global_dims[a];
-    {
-      // gather the brick's ghosted region (clamped to the cube) into pinned
-      // staging, then copy it into the scratch region
-      int64_t rlo[3], rhi[3];
-      for (int a = 0; a < 3; ++a) {
-        rlo[a] = std::max<int64_t>(hb.lo[a] - 1, 0);
-        rhi[a] = std::min<int64_t>(hb.hi[a] + 1, d.global_dims[a]);
-      }
-      const int64_t rx = rhi[0] - rlo[0], ry = rhi[1] - rlo[1], rz = rhi[2] - rlo[2];
-      const size_t need = (size_t)(rx * ry * rz) * c->src_elem_bytes;
-      if (need > c->bytes[3]) return fail(c, BC_E_NOMEM, "bc_load_bricks: scratch region too small");
-      if (c->load_staging_bytes < need) {
-        if (c->load_staging) (void)hipHostFree(c->load_staging);
-        c->load_staging = nullptr;
-        HIPCHECK(c, hipHostMalloc(&c->load_staging, c->bytes[3], hipHostMallocDefault));
-        c->load_staging_bytes = c->bytes[3];
-      }
-      const char* base = static_cast<const char*>(src);
-      char* dst = static_cast<char*>(c->load_staging);
-      const size_t eb = c->src_elem_bytes;
-      for (int64_t z = 0; z < rz; ++z)
-        for (int64_t y = 0; y < ry; ++y) {
-          const char* row = base + (((rlo[2] + z - box_lo[2]) * strides[2] + (rlo[1] + y - box_lo[1]) * strides[1] +
-                                     (rlo[0] - box_lo[0]) * strides[0]) * eb);
-          char* o = dst + ((z * ry + y) * rx) * eb;
-          if (strides[0] == 1) {
-            std::memcpy(o, row, rx * eb);
-          } else {
-            for (int64_t x = 0; x < rx; ++x) std::memcpy(o + x * eb, row + x * strides[0] * eb, eb);
-          }
-        }
-      HIPCHECK(c, hipMemcpy(c->dev[3], c->load_staging, need, hipMemcpyHostToDevice));
-      s.ptr = c->dev[3];
-      s.strides[0] = 1;
-      s.strides[1] = rx;
-      s.strides[2] = rx * ry;
-      for (int a = 0; a < 3; ++a) s.origin[a] = (int32_t)rlo[a];
-    }
-    HIPCHECK(c, convert(s, b, 1));
-    HIPCHECK(c, hipStreamSynchronize(st));
+  if (!src_on_device) {
+    const int r = load_from_host(c, src, strides, box_lo, st, convert);
+    if (r) return r;
   }
   HIPCHECK(c, hipStreamSynchronize(st));
   HIPCHECK(c, hipMemcpy(c->bricks.data(), dbricks, sizeof(BcBrick) * c->n_bricks, hipMemcpyDeviceToHost));

@@ -59,3 +59,26 @@ def test_minmax_passes_nan_by(storage):
         g = rc.ghosted_region(vol, b)
         assert mm[b.index, 0] == np.nanmin(g) and mm[b.index, 1] == np.nanmax(g)
     bc.close()
+
+
+@pytest.mark.parametrize("storage,stride", [("f32", 1), ("fp8", 2)])
+def test_host_source_gathered_by_threads(storage, stride):
+    """A host source large enough for several threads, in ragged bricks and
+    more of them than staging buffers, stores what a device source stores."""
+    import torch
+    rng = np.random.default_rng(23)
+    vol = rng.standard_normal((70, 130, 151)).astype(np.float32)
+    wide = np.full((70, 131, 151 * stride), 1e9, np.float32)
+    wide[:, :130, ::stride] = vol
+    pools = []
+    for source in (torch.from_numpy(vol).cuda(), wide[:, :130, ::stride]):
+        bc = binding.BrickCaster(0)
+        bc.plan(vol.shape[::-1], (64, 47, 33), storage=storage, max_w=16, max_h=16)
+        bc.bind()
+        for _ in range(2):
+            bc.load(source)
+        _, so, mm = bc.bricks()
+        pools.append([so, mm] + [bc.read_brick(b)[0] for b in range(len(mm))])
+        bc.close()
+    for a, b in zip(*pools):
+        assert np.array_equal(a, b)
