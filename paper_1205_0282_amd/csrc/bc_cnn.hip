@@ -64,6 +64,12 @@ __device__ __forceinline__ int2 lane_offsets(int g, int ks) {
   return make_int2(tap_offset<CIN, WIN, SIN>(t0), tap_offset<CIN, WIN, SIN>(t0 + 1));
 }
 
+// Tiles of 32 channels at 64 bytes per pixel: the 16 pixels that a 16-byte read
+// touches would start in four places of the banks' 256 bytes.  So channels
+// 8 c .. 8 c + 7 of a pixel at column x lie at its place c ^ (x / 4 % 4), which
+// spreads 16 neighbouring columns over all of it.
+__device__ __forceinline__ int swizzle(int c, int x) { return 8 * (c ^ ((x >> 2) & 3)); }
+
 template <int CIN>
 __device__ __forceinline__ bf16x8 load_a(const uint16_t* in, int pix, int2 off) {
   if (CIN >= 8) {
@@ -148,6 +154,50 @@ __device__ __forceinline__ void conv_tile(const uint16_t* in, const bf16x8 (&w)[
   }
 }
 
+// The same for a swizzled tile of 32 channels, all M-tiles of a wave at once:
+// M-tile wave + 4 j in acc[j], left in registers so that the caller can write
+// the results over the input.  Each fragment of the weights is used once, so
+// it is read AHEAD k-steps before its use and not kept (1, 2 and 3 steps: 35.7,
+// 35.0 and 36.1 us for the kernel below; left to the compiler's order, 36.6).
+template <int NT, int R, int WIN, int M, int WOUT>
+__device__ __forceinline__ void conv_hold(const uint16_t* in, const uint4* __restrict__ wf, f32x4 (&acc)[R][NT]) {
+  typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+  constexpr int KS = 9, SIN = 32, AHEAD = 2;
+  const __amdgpu_buffer_rsrc_t wr = wave_rsrc(wf, (uint32_t)(KS * NT * 64 * 16));
+  const int lane = threadIdx.x & 63, wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, r = lane & 15;
+  bf16x8 w[KS][NT];
+  auto fetch = [&](int ks) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+      w[ks][nt] = __builtin_bit_cast(bf16x8, (u4)__builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, (ks * NT + nt) * 1024, 0));
+  };
+#pragma unroll
+  for (int ks = 0; ks < AHEAD; ++ks) fetch(ks);
+  int at[R], cx[R];
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    const int p = min((wave + 4 * j) * 16 + r, M - 1);
+    at[j] = ((p / WOUT) * WIN + p % WOUT) * SIN;
+    cx[j] = p % WOUT;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[j][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    if (ks + AHEAD < KS) fetch(ks + AHEAD);
+    bf16x8 a[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+      a[j] = as_bf16x8(*reinterpret_cast<const uint4*>(in + at[j] + swizzle(g, cx[j] + ks % 3) + ((ks / 3) * WIN + ks % 3) * SIN));
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int j = 0; j < R; ++j) acc[j][nt] = mfma(w[ks][nt], a[j], acc[j][nt]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // four values as BF16
 __device__ __forceinline__ uint2 bf16_pack(float a, float b, float c, float d) {
   return make_uint2(bf16_bits(a) | (uint32_t)bf16_bits(b) << 16, bf16_bits(c) | (uint32_t)bf16_bits(d) << 16);
@@ -158,23 +208,22 @@ constexpr int PSTRIDE = 40;   // BF16 elements per pixel of a 32-channel LDS til
 
 // ------------------------------------------------------------------ inference
 // One 16x16 tile of coarse pixels per workgroup: input tile with a 3-pixel
-// halo, both hidden activations in LDS, output 32x32 fine pixels.  The next
-// layer's weights are on their way to registers during a layer.  The last
-// layer's results go to an LDS output tile (in the first activation's space,
-// free by then) and leave as whole fine pixels, with the bilinear skip read
-// from an FP32 copy of the input (in the BF16 input tile's space, free after
-// the first layer).  Bound by the latency of its phases (matrix cores busy 18%,
-// LDS 35% of the cycles): 960x540 takes 39.7 us, 44.0 with the pixels as the
-// first operand (single 16-bit stores of the activations) and the weights read
-// again for every few M-tiles; a workgroup that stays for several tiles, all
-// weights in registers, two to a compute unit, took 46.1.
+// halo, the hidden activations in LDS, output 32x32 fine pixels.  Bound by the
+// latency of its phases (matrix cores busy 18% of the cycles), so it is built
+// to have four workgroups on a compute unit: a hidden layer's results wait in
+// registers until all of its input is read and then take the input's place
+// (31 KB of LDS), and no layer's weights stay in registers (126 of them).  The last
+// layer's results go to an LDS output tile (in the activation's space again) and
+// leave as whole fine pixels, with the bilinear skip read from an FP32 copy of
+// the input (in the BF16 input tile's space, free after the first layer).
+// 960x540, whose 2040 tiles then fill the chip twice instead of 2.7 times: 39.6
+// -> 34.7 us; with two activations in LDS and three workgroups, swizzled 38.9,
+// not swizzled 39.6.
 constexpr int XF = 18;        // FP32 input pixels per side for the bilinear skip of a tile
-constexpr int ISTRIDE = 32;   // BF16 elements per pixel of the hidden activations: with 64 bytes the kernel takes
-                               // 51 KB of LDS, so that three workgroups fit a compute unit
-__global__ __launch_bounds__(256, 3) void infer_kernel(CnnInferArgs a) {
+constexpr int ISTRIDE = 32;   // BF16 elements per pixel of the hidden activations (swizzled)
+__global__ __launch_bounds__(256, 4) void infer_kernel(CnnInferArgs a) {
   __shared__ __attribute__((aligned(16))) float xbuf[XF * XF * 4];   // BF16 22x22x4 input, then FP32 18x18x4
   __shared__ __attribute__((aligned(16))) uint16_t a1[20 * 20 * ISTRIDE];
-  __shared__ __attribute__((aligned(16))) uint16_t a2[18 * 18 * ISTRIDE];
   static_assert(sizeof(uint16_t) * 22 * 22 * 4 <= sizeof(float) * XF * XF * 4, "input tile fits");
   static_assert(sizeof(a1) >= sizeof(float) * 32 * 32 * 4, "output tile fits");
   uint16_t* xs = reinterpret_cast<uint16_t*>(xbuf);
@@ -191,7 +240,7 @@ __global__ __launch_bounds__(256, 3) void infer_kernel(CnnInferArgs a) {
     in[k] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (i < 22 * 22 && gy >= 0 && gy < H && gx >= 0 && gx < W) in[k] = x[(int64_t)gy * W + gx];
   }
-  bf16x8 w1[4], w2[18];
+  bf16x8 w1[4];
   load_weights(a.wf1, w1);
   const float* __restrict__ bias = a.params;
   float bv[2][4];
@@ -209,10 +258,9 @@ __global__ __launch_bounds__(256, 3) void infer_kernel(CnnInferArgs a) {
     if (i < 22 * 22) *reinterpret_cast<uint2*>(xs + 4 * i) = bf16_pack(in[k].x, in[k].y, in[k].z, in[k].w);
   }
   __syncthreads();
-  load_weights(a.wf2, w2);
   // a hidden layer's outputs are zero outside the image (the next one's padding)
   const bool inner = oy >= 2 && ox >= 2 && oy + 18 <= H && ox + 18 <= W;
-  auto hidden = [&](uint16_t* d, int y, int z, const f32x4* v) {
+  auto hidden = [&](uint16_t* d, int col, int y, int z, const f32x4* v) {
     const bool keep = inner || (y >= 0 && y < H && z >= 0 && z < W);
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
@@ -220,13 +268,13 @@ __global__ __launch_bounds__(256, 3) void infer_kernel(CnnInferArgs a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) q[i] = fmaxf(v[nt][i] + bv[nt][i], 0.0f);
       const uint2 u = bf16_pack(q[0], q[1], q[2], q[3]);
-      *reinterpret_cast<uint2*>(d + 16 * nt + 4 * g) = make_uint2(keep ? u.x : 0u, keep ? u.y : 0u);
+      *reinterpret_cast<uint2*>(d + swizzle(2 * nt + (g >> 1), col) + 4 * (g & 1)) =
+          make_uint2(keep ? u.x : 0u, keep ? u.y : 0u);
     }
   };
-  conv_tile<4, 2, 2, 4, 22, 4, 400, 20>(xs, w1, [&](int p, const f32x4* v) {
-    hidden(a1 + p * ISTRIDE, oy - 2 + p / 20, ox - 2 + p % 20, v);
+  conv_tile<4, 2, 2, 7, 22, 4, 400, 20>(xs, w1, [&](int p, const f32x4* v) {
+    hidden(a1 + p * ISTRIDE, p % 20, oy - 2 + p / 20, ox - 2 + p % 20, v);
   });
-  biases(CNN_OFF_B2, 2);
   __syncthreads();
   // FP32 input rows oy-1 .. oy+16 and columns ox-1 .. ox+16, clamped to the
   // image as the bilinear skip clamps them
@@ -234,22 +282,35 @@ __global__ __launch_bounds__(256, 3) void infer_kernel(CnnInferArgs a) {
     const int gy = min(max(oy - 1 + i / XF, 0), H - 1), gx = min(max(ox - 1 + i % XF, 0), W - 1);
     reinterpret_cast<float4*>(xbuf)[i] = x[(int64_t)gy * W + gx];
   }
-  conv_tile<32, 9, 2, 2, 20, ISTRIDE, 324, 18>(a1, w2, [&](int p, const f32x4* v) {
-    hidden(a2 + p * ISTRIDE, oy - 1 + p / 18, ox - 1 + p % 18, v);
-  });
-  bf16x8 w3[9];
-  load_weights(a.wf3, w3);
-  biases(CNN_OFF_B3, 1);
+  const int wave = (int)__builtin_amdgcn_readfirstlane(tid >> 6), r = tid & 15;
+  {
+    f32x4 acc[6][2];
+    conv_hold<2, 6, 20, 324, 18>(a1, a.wf2, acc);
+    biases(CNN_OFF_B2, 2);
+    __syncthreads();   // (all of a1 read: the second activation takes its place)
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+      const int p = (wave + 4 * j) * 16 + r;
+      if (p < 324) hidden(a1 + p * ISTRIDE, p % 18, oy - 1 + p / 18, ox - 1 + p % 18, acc[j]);
+    }
+  }
   __syncthreads();
   float* ot = reinterpret_cast<float*>(a1);   // [32][32] fine pixels x 4 channels
-  // channel 4c + 2dy + dx goes to fine pixel (2i + dy, 2j + dx), channel c: the lane's four are c = g
-  conv_tile<32, 9, 1, 4, 18, ISTRIDE, 256, 16>(a2, w3, [&](int p, const f32x4* v) {
-    float* d = ot + ((2 * (p >> 4)) * 32 + 2 * (p & 15)) * 4 + g;
-    d[0] = v[0][0] + bv[0][0];
-    d[4] = v[0][1] + bv[0][1];
-    d[128] = v[0][2] + bv[0][2];
-    d[132] = v[0][3] + bv[0][3];
-  });
+  {
+    f32x4 acc[4][1];
+    conv_hold<1, 4, 18, 256, 16>(a1, a.wf3, acc);
+    biases(CNN_OFF_B3, 1);
+    __syncthreads();
+    // channel 4c + 2dy + dx goes to fine pixel (2i + dy, 2j + dx), channel c: the lane's four are c = g
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      float* d = ot + ((2 * (wave + 4 * j)) * 32 + 2 * r) * 4 + g;
+      d[0] = acc[j][0][0] + bv[0][0];
+      d[4] = acc[j][0][1] + bv[0][1];
+      d[128] = acc[j][0][2] + bv[0][2];
+      d[132] = acc[j][0][3] + bv[0][3];
+    }
+  }
   __syncthreads();
   // out = shuffled network output + bilinear x2 of x (half-pixel centres,
   // clamp to edge), whole fine pixels per thread; fine coordinates lie a

@@ -60,6 +60,13 @@ def test_inference_matches_oracle(caster, shape):
         assert np.abs(out[i] - ref).max() <= 2e-2
 
 
+@pytest.mark.parametrize("shape", [(1, 1, 1), (2, 3, 35), (1, 17, 15), (1, 33, 16)])
+def test_inference_of_partial_tiles(caster, shape):
+    """Images smaller than a tile and tiles cut at one or both edges, whose
+    hidden activations outside the image are padding."""
+    test_inference_matches_oracle(caster, shape)
+
+
 def test_zero_last_layer_is_exact_bilinear(caster):
     import torch
     p = _params(4)
