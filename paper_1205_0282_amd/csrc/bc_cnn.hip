@@ -154,15 +154,15 @@ __device__ __forceinline__ void conv_tile(const uint16_t* in, const bf16x8 (&w)[
   }
 }
 
-// The same for a swizzled tile of 32 channels, all M-tiles of a wave at once:
+// The same for a tile of 32 channels (swizzled at 64 bytes per pixel), all M-tiles of a wave at once:
 // M-tile wave + 4 j in acc[j], left in registers so that the caller can write
 // the results over the input.  Each fragment of the weights is used once, so
 // it is read AHEAD k-steps before its use and not kept (1, 2 and 3 steps: 35.7,
 // 35.0 and 36.1 us for the kernel below; left to the compiler's order, 36.6).
-template <int NT, int R, int WIN, int M, int WOUT>
+template <int NT, int R, int WIN, int SIN, int M, int WOUT>
 __device__ __forceinline__ void conv_hold(const uint16_t* in, const uint4* __restrict__ wf, f32x4 (&acc)[R][NT]) {
   typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-  constexpr int KS = 9, SIN = 32, AHEAD = 2;
+  constexpr int KS = 9, AHEAD = 2;
   const __amdgpu_buffer_rsrc_t wr = wave_rsrc(wf, (uint32_t)(KS * NT * 64 * 16));
   const int lane = threadIdx.x & 63, wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, r = lane & 15;
@@ -189,7 +189,8 @@ __device__ __forceinline__ void conv_hold(const uint16_t* in, const uint4* __res
     bf16x8 a[R];
 #pragma unroll
     for (int j = 0; j < R; ++j)
-      a[j] = as_bf16x8(*reinterpret_cast<const uint4*>(in + at[j] + swizzle(g, cx[j] + ks % 3) + ((ks / 3) * WIN + ks % 3) * SIN));
+      a[j] = as_bf16x8(*reinterpret_cast<const uint4*>(in + at[j] + (SIN == 32 ? swizzle(g, cx[j] + ks % 3) : 8 * g) +
+                                                   ((ks / 3) * WIN + ks % 3) * SIN));
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -285,7 +286,7 @@ __global__ __launch_bounds__(256, 4) void infer_kernel(CnnInferArgs a) {
   const int wave = (int)__builtin_amdgcn_readfirstlane(tid >> 6), r = tid & 15;
   {
     f32x4 acc[6][2];
-    conv_hold<2, 6, 20, 324, 18>(a1, a.wf2, acc);
+    conv_hold<2, 6, 20, ISTRIDE, 324, 18>(a1, a.wf2, acc);
     biases(CNN_OFF_B2, 2);
     __syncthreads();   // (all of a1 read: the second activation takes its place)
 #pragma unroll
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(256, 4) void infer_kernel(CnnInferArgs a) {
   float* ot = reinterpret_cast<float*>(a1);   // [32][32] fine pixels x 4 channels
   {
     f32x4 acc[4][1];
-    conv_hold<1, 4, 18, 256, 16>(a1, a.wf3, acc);
+    conv_hold<1, 4, 18, ISTRIDE, 256, 16>(a1, a.wf3, acc);
     biases(CNN_OFF_B3, 1);
     __syncthreads();
     // channel 4c + 2dy + dx goes to fine pixel (2i + dy, 2j + dx), channel c: the lane's four are c = g
@@ -363,28 +364,35 @@ __device__ void stage_tile(uint16_t* t, int sin, const float* __restrict__ img, 
   }
 }
 
-// At 960x540: forward 14.4, 22.4 and (with the loss) 32.8 us, backward 17.7 and
-// 26 us; 14.6, 24, 37.6, 28.6 and 33 with a lane's results in one channel of
-// four pixels (2-byte stores, 4-byte loads of the target).
+// Bound by HBM and the latency of a tile's phases.  At 960x540: forward 14.7,
+// 21.7 and (with the loss) 25.9 us, backward 17.6 and 25.2 us.  The layers of 32
+// input channels stream their weights and the loss layer keeps its outputs and
+// gradients in its input's place, so that four workgroups share a compute
+// unit: with the weights in registers and LDS of their own 22.3, 32.8 and 26.0.
+// With a lane's results in one channel of four pixels (2-byte stores, 4-byte
+// loads of the target) 14.6, 24, 37.6, 28.6 and 33.
 // mode 0: a = bf16(relu(z + b)) stored NHWC (COUT channels)
 // mode 1: g = bf16(z * [mask > 0]) stored NHWC (backward-data with ReLU mask)
 // mode 2: last layer + loss: y = z + b, out = shuffle(y) + bilinear(x),
 //         g_y = bf16(2 (out - target) / count), squared error summed per tile
 template <int CIN, int COUT, int KS, int MODE>
-__global__ __launch_bounds__(256) void layer_kernel(CnnLayerArgs a) {
+__global__ __launch_bounds__(256, CIN == 32 ? 4 : 1) void layer_kernel(CnnLayerArgs a) {
   constexpr int SIN = CIN == 4 ? 4 : PSTRIDE;
   constexpr int NT = COUT / 16;
   __shared__ __attribute__((aligned(16))) uint16_t t[18 * 18 * SIN];
-  // last layer: its outputs as fine pixels, the image around them, and their gradients
-  __shared__ float4 ot[MODE == 2 ? 32 * 32 : 1], xi[MODE == 2 ? 18 * 18 : 1];
-  __shared__ __attribute__((aligned(16))) uint16_t gt[MODE == 2 ? 256 * 16 : 8];
+  // last layer: the image around the tile, and in the input's place its
+  // outputs as fine pixels and their gradients
+  __shared__ float4 xi[MODE == 2 ? 18 * 18 : 1];
   __shared__ float red[MODE == 2 ? 256 : 1];
+  float4* ot = reinterpret_cast<float4*>(t);
+  uint16_t* gt = t + 32 * 32 * 8;
+  static_assert(MODE != 2 || 18 * 18 * SIN >= 32 * 32 * 8 + 256 * 16, "outputs and gradients fit");
   const int H = a.h, W = a.w;
   const int n = blockIdx.z;
   const int oy = blockIdx.y * 16, ox = blockIdx.x * 16;
   const int64_t plane = (int64_t)H * W;
-  bf16x8 w[KS * NT];
-  load_weights(a.wf, w);
+  bf16x8 w[CIN == 32 ? 1 : KS * NT];
+  if constexpr (CIN != 32) load_weights(a.wf, w);
   stage_tile<CIN>(t, SIN, a.img ? a.img + n * plane * 4 : nullptr, a.in ? a.in + n * plane * CIN : nullptr, H, W, oy, ox);
   if (MODE == 2)
     for (int i = threadIdx.x; i < 18 * 18; i += 256) {
@@ -398,7 +406,7 @@ __global__ __launch_bounds__(256) void layer_kernel(CnnLayerArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) bv[nt][i] = MODE == 1 ? 0.0f : a.bias[16 * nt + 4 * g + i];
   __syncthreads();
-  conv_tile<CIN, KS, NT, 4, 18, SIN, 256, 16>(t, w, [&](int p, const f32x4* v) {
+  auto result = [&](int p, const f32x4* v) {
     if (MODE == 2) {
       // channel 4c + 2dy + dx is channel c of fine pixel (2 gy + dy, 2 gx + dx): the lane's four are c = g
       float* d = reinterpret_cast<float*>(ot) + ((2 * (p >> 4)) * 32 + 2 * (p & 15)) * 4 + g;
@@ -427,7 +435,16 @@ __global__ __launch_bounds__(256) void layer_kernel(CnnLayerArgs a) {
                          (m.y & 0x7fffu) ? v[nt][2] : 0.0f, (m.y & 0x7fff0000u) ? v[nt][3] : 0.0f);
       }
     }
-  });
+  };
+  if constexpr (CIN == 32) {
+    f32x4 acc[4][NT];
+    conv_hold<NT, 4, 18, SIN, 256, 16>(t, a.wf, acc);
+    if (MODE == 2) __syncthreads();   // (all of the input read)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) result(((int)(threadIdx.x >> 6) + 4 * j) * 16 + (int)(threadIdx.x & 15), acc[j]);
+  } else {
+    conv_tile<CIN, KS, NT, 4, 18, SIN, 256, 16>(t, w, result);
+  }
   if (MODE == 2) {
     // whole fine pixels per thread, so that the target is read and the
     // gradient written in whole lines
