@@ -12,6 +12,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <exception>
 #include <map>
 #include <mutex>
 #include <string>
@@ -924,7 +925,12 @@ int bc_load_bricks(bc_ctx* c, const void* src, const int64_t strides[3], int src
   }
   // a host source goes through the load scratch region one brick at a time
   if (!src_on_device) {
-    const int r = load_from_host(c, src, strides, box_lo, st, convert);
+    int r = BC_OK;
+    try {
+      r = load_from_host(c, src, strides, box_lo, st, convert);
+    } catch (const std::exception& e) {   // (no host memory for the list of bricks)
+      r = fail(c, BC_E_NOMEM, "bc_load_bricks: %s", e.what());
+    }
     if (r) return r;
   }
   HIPCHECK(c, hipStreamSynchronize(st));
