@@ -89,7 +89,7 @@ MEASURED_TRAFFIC = {
         "cube3000x3000x1500_f16_4views/f16/composite/fixed": 0.6563,
     },
 }
-KERNEL_SOURCES = ("bc_render.hip", "bc_types.h", "bc_kernels.h", "bc_df.h", "bc_e4m3.h")
+KERNEL_SOURCES = ("bc_render.hip", "bc_types.h", "bc_kernels.h", "bc_ray.h", "bc_e4m3.h")
 
 
 def kernel_sha256() -> str:
