@@ -262,7 +262,10 @@ int bc_set_option(bc_ctx* ctx, int option, int64_t value);
  * work items fit the planned sub-image tiles) times samples per occupancy chunk
  * in {32, 64} times persistent workgroups in {2, 4, 6, 8} per compute unit --
  * for `frames` timed frames each (after one warm-up frame per candidate),
- * measures the ray-casting kernel with HIP events and keeps the fastest;
+ * measures the ray-casting kernel with HIP events and keeps the fastest; the
+ * launches are those of captured frames if BC_OPT_GRAPH is on, and workgroup
+ * counts that lead to the same launch are timed once, the count set before
+ * being kept if it is one of them;
  * chosen[0] = chunk, chosen[1] = workgroups, chosen[2] = tile width in pixels
  * (chosen may be NULL; else it has 3 entries).  Writes frames into `out` (same
  * contract as bc_render_frame) and waits for them.  The result applies to

@@ -144,8 +144,9 @@ struct bc_ctx {
   // ray operator and step policy (bc_set_operator)
   int op = BC_OP_COMPOSITE;
   int step_policy = BC_STEP_FIXED;
-  // captured frames (one per input slot)
-  bool use_graph = false;
+  // captured frames (one per input slot); bc_autotune times their launches
+  // without capturing them
+  bool use_graph = false, as_captured = false;
   hipStream_t capture_stream = nullptr;
   // learned frames: second stream for the validation pass, and the events
   // that fork it from and join it back to the frame's stream
@@ -340,6 +341,30 @@ BcFramePtrs frame_ptrs(bc_ctx* c) {
   f.width = c->views.empty() ? 0 : c->views[0].width;
   f.height = c->views.empty() ? 0 : c->views[0].height;
   return f;
+}
+
+// Workgroups of a persistent ray-casting launch: a wave takes one work item at a
+// time, so no more than the items can occupy (a captured frame is replayed for
+// other views: the full count).
+int persistent_workgroups(int64_t items, int most, bool captured) {
+  return captured ? most : (int)std::min<int64_t>(most, std::max<int64_t>((items + 3) / 4, 1));
+}
+
+// Few samples in all, and a workgroup takes each item with four lanes to a
+// ray (render_quad_kernel) instead of the persistent launch, whose time is
+// then that of a few long items.  `items` bounds the pass's items; a ray
+// crosses a brick in up to about an edge's worth of samples.
+bool takes_quads(const bc_ctx* c, int64_t items, double step, bool captured) {
+  double edge = 0.0;
+  for (int a = 0; a < 3; ++a)
+    edge += (double)std::min<int64_t>(c->desc.brick_dims[a], c->desc.share_hi[a] - c->desc.share_lo[a]) / 3.0;
+  const double per_ray = edge / (c->step_policy == BC_STEP_PER_VOXEL ? 1.0 : step);
+  // (projection at one sample per voxel through large bricks, from FP32 and
+  // FP16: its rays gather so few samples per line that the quads' better
+  // spread pays at any size)
+  const bool sparse = c->op == BC_OP_MIP && c->step_policy == BC_STEP_PER_VOXEL && c->desc.storage != BC_FP8_E4M3 &&
+                      edge >= kQuadMipEdge;
+  return !captured && c->chunk == 32 && ((double)items * per_ray <= kQuadSamples || sparse);
 }
 
 int wait_frame(bc_ctx* c) {
@@ -1110,28 +1135,9 @@ int render_impl(bc_ctx* c, float* out, void* stream, float4* sub, int64_t sub_ca
   }
   // the frame: the kernels of every pass (each pass's set-up kernel first
   // copies the pass inputs from the pinned slot)
-  // a wave takes one work item at a time: no more workgroups than the items
-  // can occupy (a captured frame is replayed for other views: the full count)
-  const bool captured = c->use_graph && !no_alloc;
-  auto workgroups = [&](int64_t items, int most) -> int {
-    return captured ? most : (int)std::min<int64_t>(most, std::max<int64_t>((items + 3) / 4, 1));
-  };
-  // Few samples in all, and a workgroup takes each item with four lanes to a
-  // ray (render_quad_kernel) instead of the persistent launch, whose time is
-  // then that of a few long items.  `items` bounds the pass's items; a ray
-  // crosses a brick in up to about an edge's worth of samples.
-  double edge = 0.0;
-  for (int a = 0; a < 3; ++a)
-    edge += (double)std::min<int64_t>(c->desc.brick_dims[a], c->desc.share_hi[a] - c->desc.share_lo[a]) / 3.0;
+  const bool captured = (c->use_graph || c->as_captured) && !no_alloc;
   auto route = [&](BcFramePtrs& p, int64_t items, double step) {
-    const double per_ray = edge / (c->step_policy == BC_STEP_PER_VOXEL ? 1.0 : step);
-    // (projection at one sample per voxel through large bricks, from FP32 and
-    // FP16: its rays gather so few samples per line that the quads' better
-    // spread pays at any size)
-    const bool sparse = c->op == BC_OP_MIP && c->step_policy == BC_STEP_PER_VOXEL && c->desc.storage != BC_FP8_E4M3 &&
-                        edge >= kQuadMipEdge;
-    const bool quad = !captured && c->chunk == 32 && ((double)items * per_ray <= kQuadSamples || sparse);
-    p.item_bound = quad ? std::min<int64_t>(std::max<int64_t>(items, 1), 1 << 20) : 0;
+    p.item_bound = takes_quads(c, items, step, captured) ? std::min<int64_t>(std::max<int64_t>(items, 1), 1 << 20) : 0;
   };
   auto enqueue = [&](hipStream_t s, hipEvent_t* e) -> int {
     if (e && c->timing_stages) HIPCHECK(c, hipEventRecord(e[0], s));
@@ -1139,7 +1145,7 @@ int render_impl(bc_ctx* c, float* out, void* stream, float4* sub, int64_t sub_ca
       route(f, c->view_tiles, dt);
       HIPCHECK(c, bc_launch_setup(f, s));
       if (e) HIPCHECK(c, hipEventRecord(e[1], s));
-      HIPCHECK(c, bc_launch_render(f, workgroups(c->view_tiles, c->render_workgroups), s));
+      HIPCHECK(c, bc_launch_render(f, persistent_workgroups(c->view_tiles, c->render_workgroups, captured), s));
       if (e) HIPCHECK(c, hipEventRecord(e[2], s));
       HIPCHECK(c, bc_launch_composite(f, reinterpret_cast<float4*>(out), s));
     } else {
@@ -1399,7 +1405,9 @@ int bc_autotune(bc_ctx* c, float* out, void* stream, int frames, int64_t chosen[
   const bool timing = c->timing, graph = c->use_graph;
   const int chunk0 = c->chunk, wgs0 = c->render_workgroups, shift0 = c->tile_shift;
   const int64_t tiles0 = c->view_tiles;
+  // (the launches that later frames will have: a captured frame's, if they are captured)
   c->use_graph = false;
+  c->as_captured = graph;
   const int shifts[3] = {3, 4, 2};   // 8 x 8, 16 x 4, 4 x 16 screen tiles
   const int chunks[2] = {32, 64};
   const int per_cu[4] = {2, 4, 6, 8};
@@ -1414,10 +1422,18 @@ int bc_autotune(bc_ctx* c, float* out, void* stream, int frames, int64_t chosen[
     for (const bc_view& v : c->views) tiles += view_tiles_bound(c, v);
     if (tiles > c->max_tiles) continue;   // this shape does not fit the planned sub-image tiles
     c->view_tiles = tiles;
-    for (int ci = 0; ci < 2 && !r; ++ci)
+    for (int ci = 0; ci < 2 && !r; ++ci) {
+      c->chunk = chunks[ci];
+      // workgroups that a count leads to: none of them tells launches apart
+      // that have one workgroup per item, or no more than the items occupy
+      const bool quads = takes_quads(c, tiles, c->views[0].step, graph);
+      auto launched = [&](int wgs) { return quads ? 0 : persistent_workgroups(tiles, wgs, graph); };
+      int timed = -1;
       for (int wi = 0; wi < 4 && !r; ++wi) {
-        c->chunk = chunks[ci];
-        c->render_workgroups = c->n_cu * per_cu[wi];
+        const int wgs = c->n_cu * per_cu[wi];
+        if (launched(wgs) == timed) continue;
+        timed = launched(wgs);
+        c->render_workgroups = wgs;
         c->timing = true;
         c->timed_frames = 0;
         for (int k = 0; k < frames + 1 && !r; ++k) {
@@ -1431,12 +1447,15 @@ int bc_autotune(bc_ctx* c, float* out, void* stream, int frames, int64_t chosen[
         if (!r && nf > 0 && ms[1] / nf < best) {
           best = ms[1] / nf;
           best_chunk = c->chunk;
-          best_wgs = c->render_workgroups;
+          // (where the count in use leads to the same launch, it stays)
+          best_wgs = launched(wgs0) == timed ? wgs0 : wgs;
           best_shift = c->tile_shift;
           best_tiles = c->view_tiles;
         }
       }
+    }
   }
+  c->as_captured = false;
   c->timing = timing;
   c->timed_frames = 0;
   c->use_graph = graph;
