@@ -78,12 +78,17 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 constexpr int kMaxTimedFrames = 4096;
 constexpr int kPasses = 3;   // learned frame: coarse, validation, conditional plain
 
-// Where the ray caster's two forms meet, in work items times a brick's edge in
-// samples (render us, persistent / four lanes to a ray, FP32 compositing):
-// 128^3 bricks 9.7 K items 227 / 180, 15 K 260 / 251, 20 K 295 / 309; 250^3
-// bricks 2.9 K items 390 / 232, 9.2 K 256 / 277; 64^3 bricks 25 K items
-// 221 / 191; FP16 100^3 bricks 14 K items 223 / 188, 30 K 300 / 362.
-constexpr double kQuadSamples = 4.7e6;
+// Where the ray caster's two forms meet: kQuadItems is items times an item's
+// cost in four lanes to a ray, in samples (takes_quads has the cost).  Fitted to
+// 4137 frames (1 to 216 bricks of 12 to 900 voxels, FP32, FP16 and FP8, steps
+// 0.5 to 2, one view and four, close and far): of the 2877 it gives the quads,
+// two are more than 2% slower than the persistent launch (4% at most).  Render
+// us, persistent / quads, FP32 compositing on both sides of the line: 8 bricks
+// of 64^3, step 0.5, 28 K items 214 / 166; 64 of 64^3, step 0.5, 29 K 231 / 200
+// and 33 K 246 / 238; 64 of 64^3, step 2, 50 K 231 / 223 and 76 K 269 / 337; 64
+// of 128^3, step 1, 27 K 221 / 229 and 31 K 236 / 261; 64 of 250^3, step 0.5,
+// 9.3 K 362 / 290 and 20 K 526 / 629; one brick of 96^3, step 1, 130 K 1586 / 1017.
+constexpr double kQuadItems = 9.7e6;
 // Projection at one sample per voxel: 256^3 bricks, 82 K items, FP32 1505 /
 // 1384, FP16 1234 / 1177, FP8 1052 / 1078; 125^3 bricks, 71 K items, FP32 569 / 630.
 constexpr double kQuadMipEdge = 192.0;
@@ -355,16 +360,25 @@ int persistent_workgroups(int64_t items, int most, bool captured) {
 // then that of a few long items.  `items` bounds the pass's items; a ray
 // crosses a brick in up to about an edge's worth of samples.
 bool takes_quads(const bc_ctx* c, int64_t items, double step, bool captured) {
+  if (captured || c->chunk != 32) return false;
   double edge = 0.0;
   for (int a = 0; a < 3; ++a)
     edge += (double)std::min<int64_t>(c->desc.brick_dims[a], c->desc.share_hi[a] - c->desc.share_lo[a]) / 3.0;
-  const double per_ray = edge / (c->step_policy == BC_STEP_PER_VOXEL ? 1.0 : step);
+  const bool per_voxel = c->step_policy == BC_STEP_PER_VOXEL;
+  const double ray = edge / (per_voxel ? 1.0 : step);
+  // An item's ray set-ups and idle lanes cost what 165 samples of its rays do;
+  // long rays cost more than their samples, as the persistent kernel's lanes
+  // find the last cell and word in registers where these gather them again.
+  // Few bricks leave queues empty (one for each brick, of eight), and the
+  // persistent launch pays 14 ns a claim of each queue: while rays are short that
+  // is what it takes.
+  const double queues = (double)std::min(c->n_bricks, 8);
+  const double claims = ray <= 200.0 ? std::max(770.0 / queues - 60.0 - 0.36 * ray, 0.0) : 0.0;
+  if ((double)items * (165.0 + ray + ray * ray / 1000.0 - claims) <= kQuadItems) return true;
   // (projection at one sample per voxel through large bricks, from FP32 and
   // FP16: its rays gather so few samples per line that the quads' better
   // spread pays at any size)
-  const bool sparse = c->op == BC_OP_MIP && c->step_policy == BC_STEP_PER_VOXEL && c->desc.storage != BC_FP8_E4M3 &&
-                      edge >= kQuadMipEdge;
-  return !captured && c->chunk == 32 && ((double)items * per_ray <= kQuadSamples || sparse);
+  return c->op == BC_OP_MIP && per_voxel && c->desc.storage != BC_FP8_E4M3 && edge >= kQuadMipEdge;
 }
 
 int wait_frame(bc_ctx* c) {
