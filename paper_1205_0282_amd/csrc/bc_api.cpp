@@ -89,9 +89,9 @@ constexpr int kPasses = 3;   // learned frame: coarse, validation, conditional p
 // of 128^3, step 1, 27 K 221 / 229 and 31 K 236 / 261; 64 of 250^3, step 0.5,
 // 9.3 K 362 / 290 and 20 K 526 / 629; one brick of 96^3, step 1, 130 K 1586 / 1017.
 constexpr double kQuadItems = 9.7e6;
-// Projection at one sample per voxel: 256^3 bricks, 82 K items, FP32 1505 /
-// 1384, FP16 1234 / 1177, FP8 1052 / 1078; 125^3 bricks, 71 K items, FP32 569 / 630.
-constexpr double kQuadMipEdge = 192.0;
+// Projection at one sample per voxel from FP32 and FP16: bricks' edge, rays'
+// spacing in voxels (takes_quads says when).
+constexpr double kQuadMipEdge = 192.0, kQuadMipSpacing = 1.75, kQuadMipF16 = 500.0;
 
 }  // namespace
 
@@ -355,6 +355,21 @@ int persistent_workgroups(int64_t items, int most, bool captured) {
   return captured ? most : (int)std::min<int64_t>(most, std::max<int64_t>((items + 3) / 4, 1));
 }
 
+// voxels between neighbouring rays at the share's centre, the closest of the
+// views (0 behind the eye)
+double ray_spacing(const bc_ctx* c) {
+  double least = INFINITY;
+  for (const bc_view& v : c->views) {
+    double M[16], P[16], depth = 0.0;
+    rowmajor(v.modelview, M);
+    rowmajor(v.projection, P);
+    for (int a = 0; a < 3; ++a) depth -= M[8 + a] * 0.5 * (double)(c->desc.share_lo[a] + c->desc.share_hi[a]);
+    const double w = P[14] == -1.0 ? std::max(depth - M[11], 0.0) : 1.0;   // (orthographic: the same at any depth)
+    least = std::min(least, w * 2.0 / std::sqrt(std::fabs(P[0] * v.width * P[5] * v.height)));
+  }
+  return least;
+}
+
 // Few samples in all, and a workgroup takes each item with four lanes to a
 // ray (render_quad_kernel) instead of the persistent launch, whose time is
 // then that of a few long items.  `items` bounds the pass's items; a ray
@@ -375,10 +390,16 @@ bool takes_quads(const bc_ctx* c, int64_t items, double step, bool captured) {
   const double queues = (double)std::min(c->n_bricks, 8);
   const double claims = ray <= 200.0 ? std::max(770.0 / queues - 60.0 - 0.36 * ray, 0.0) : 0.0;
   if ((double)items * (165.0 + ray + ray * ray / 1000.0 - claims) <= kQuadItems) return true;
-  // (projection at one sample per voxel through large bricks, from FP32 and
-  // FP16: its rays gather so few samples per line that the quads' better
-  // spread pays at any size)
-  return c->op == BC_OP_MIP && per_voxel && c->desc.storage != BC_FP8_E4M3 && edge >= kQuadMipEdge;
+  // Projection at one sample per voxel through large bricks, with rays so far
+  // apart that they share few lines: the quads' better spread pays at any size,
+  // from FP16 (whose lines hold twice the voxels) only for larger bricks or rays
+  // further apart.  Render, quads / persistent, FP32 and FP16: 1024^3 in 205^3,
+  // spacing 1.79 0.88 and 0.99, 1.36 1.12 and 1.31; 1721x1721x1025 in 256^3,
+  // 2.03 0.87 and 0.93, 1.67 0.96 and 1.10, 1.27 1.08 and 1.25; in 192^3, 2.67
+  // 0.92 and 0.95, 2.14 0.97 and 1.06, 1.67 1.01 and 1.18.  FP8 bricks: 1.03 and more.
+  if (c->op != BC_OP_MIP || !per_voxel || c->desc.storage == BC_FP8_E4M3 || edge < kQuadMipEdge) return false;
+  const double spacing = ray_spacing(c);
+  return spacing >= kQuadMipSpacing && (c->desc.storage == BC_F32 || spacing * edge >= kQuadMipF16);
 }
 
 int wait_frame(bc_ctx* c) {

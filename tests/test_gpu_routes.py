@@ -27,6 +27,8 @@ def _ms(bc, out, chunk):
 @pytest.mark.parametrize("edge,brick,storage,op,size,zoom,step,low,high", [
     (64, 16, "f32", ("composite", "fixed"), (1920, 1080), 3.0, 1.0, 0.5, 1.3),     # many items of few samples
     (64, 16, "fp8", ("composite", "fixed"), (1024, 768), 3.0, 2.0, 0.5, 1.3),
+    (512, 256, "f32", ("mip", "voxel"), (1920, 1080), 4.0, 0.5, 0.5, 1.2),         # a close view
+    (512, 256, "f16", ("mip", "voxel"), (1920, 1080), 4.0, 0.5, 0.5, 1.2),
     (128, 64, "f32", ("composite", "fixed"), (256, 256), 1.0, 0.5, 0.0, 0.9),     # few items: the quads
     (96, 96, "f32", ("composite", "fixed"), (1920, 1080), 3.0, 2.0, 0.0, 0.9),    # one brick, one queue
 ])
