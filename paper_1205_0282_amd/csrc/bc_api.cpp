@@ -6,9 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
-#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -21,6 +19,7 @@
 
 #include "../../include/brickcast.h"
 #include "bc_cnn.h"
+#include "bc_gather.h"
 #include "bc_kernels.h"
 #include "bc_types.h"
 
@@ -127,7 +126,7 @@ struct bc_ctx {
   bool frame_pending = false;
   int frame_views = 0;
   // host-source load staging (pinned): one brick's region is gathered while
-  // the one before is on its way to the device
+  // the one before is on its way to the device (a single brick has one buffer)
   void* load_staging[2] = {nullptr, nullptr};
   hipEvent_t load_copied[2] = {nullptr, nullptr};
   // transfer function and views (host copies)
@@ -533,91 +532,6 @@ CnnLayout cnn_layout(int n, int h, int w) {
 
 int cnn_infer(bc_ctx* c, const CnnLayout& L, const float* coarse, float* fine, int n, int h, int w, hipStream_t st);
 
-// Threads that gather a host source's bricks into the staging buffers, each
-// brick in `kParts` runs of rows.  Brick b goes to buffer b % 2 and is taken up
-// once release() has let it.
-class Gather {
- public:
-  static constexpr int kParts = 16;
-  struct Brick {
-    const char* src;               // first element of the region
-    int64_t row, plane, elem;      // byte strides of the source
-    int64_t rx, ry, rz, bytes;     // region, bytes per element
-  };
-
-  Gather(std::vector<Brick> bricks, void* const* buffers, int threads) : bricks_(std::move(bricks)), left_(bricks_.size(), kParts) {
-    buffer_[0] = static_cast<char*>(buffers[0]);
-    buffer_[1] = static_cast<char*>(buffers[1]);
-    try {
-      for (int i = 0; i < threads; ++i) threads_.emplace_back([this] { work(); });
-    } catch (...) {   // (as many as there are; wait() does the work where there are none)
-    }
-  }
-  ~Gather() {
-    {
-      std::lock_guard<std::mutex> lock(mu_);
-      stop_ = true;
-    }
-    cv_.notify_all();
-    for (std::thread& t : threads_) t.join();
-  }
-  // bricks below n may be gathered
-  void release(int n) {
-    {
-      std::lock_guard<std::mutex> lock(mu_);
-      released_ = n;
-    }
-    cv_.notify_all();
-  }
-  // until brick b is in its buffer
-  void wait(int b) {
-    if (threads_.empty()) {
-      for (int k = 0; k < kParts; ++k) part(b, k);
-      return;
-    }
-    std::unique_lock<std::mutex> lock(mu_);
-    cv_.wait(lock, [&] { return left_[b] == 0; });
-  }
-
- private:
-  void part(int b, int k) {
-    const Brick& g = bricks_[b];
-    const int64_t rows = g.ry * g.rz, n = g.rx * g.bytes;
-    char* out = buffer_[b & 1] + rows * k / kParts * n;
-    for (int64_t r = rows * k / kParts; r < rows * (k + 1) / kParts; ++r, out += n) {
-      const char* in = g.src + (r / g.ry) * g.plane + (r % g.ry) * g.row;
-      if (g.elem == g.bytes) std::memcpy(out, in, (size_t)n);
-      else
-        for (int64_t x = 0; x < g.rx; ++x) std::memcpy(out + x * g.bytes, in + x * g.elem, (size_t)g.bytes);
-    }
-  }
-  void work() {
-    const int64_t total = (int64_t)bricks_.size() * kParts;
-    for (;;) {
-      const int64_t t = next_.fetch_add(1);
-      if (t >= total) return;
-      const int b = (int)(t / kParts);
-      {
-        std::unique_lock<std::mutex> lock(mu_);
-        cv_.wait(lock, [&] { return stop_ || b < released_; });
-        if (stop_) return;
-      }
-      part(b, (int)(t % kParts));
-      std::lock_guard<std::mutex> lock(mu_);
-      if (--left_[b] == 0) cv_.notify_all();
-    }
-  }
-  std::vector<Brick> bricks_;
-  std::vector<int> left_;          // parts of each brick still to do
-  char* buffer_[2];
-  std::vector<std::thread> threads_;
-  std::mutex mu_;
-  std::condition_variable cv_;
-  std::atomic<int64_t> next_{0};
-  int released_ = 0;
-  bool stop_ = false;
-};
-
 // Bricks of a host source: each one's ghosted region (clamped to the cube) is
 // gathered into pinned staging, copied into the scratch region and converted,
 // the next one being gathered meanwhile.  One thread's row copies (12 GB/s,
@@ -663,27 +577,37 @@ int load_from_host(bc_ctx* c, const void* src, const int64_t* strides, const int
     bricks.push_back(g);
     from.push_back(s);
   }
-  for (int i = 0; i < 2; ++i) {
-    if (!c->load_staging[i]) HIPCHECK(c, hipHostMalloc(&c->load_staging[i], c->bytes[3], hipHostMallocDefault));
+  // one buffer for one brick, and where the host has no more pinned memory: the
+  // next brick is then gathered once the one before has left it
+  const int n = (int)bricks.size();
+  int buffers = 0;
+  for (; buffers < std::min(n, 2); ++buffers) {
+    const int i = buffers;
     if (!c->load_copied[i]) HIPCHECK(c, hipEventCreateWithFlags(&c->load_copied[i], hipEventDisableTiming));
+    if (c->load_staging[i]) continue;
+    const hipError_t e = hipHostMalloc(&c->load_staging[i], c->bytes[3], hipHostMallocDefault);
+    if (e == hipSuccess) continue;
+    c->load_staging[i] = nullptr;
+    (void)hipGetLastError();
+    if (i == 0) HIPCHECK(c, e);
+    break;
   }
   // (a thread to start costs about what it copies of 256 KB)
   const int threads = all < (int64_t(2) << 20) ? 0
                       : (int)std::min<int64_t>({8, all >> 20, std::max<int64_t>(std::thread::hardware_concurrency(), 1)});
-  const int n = (int)bricks.size();
-  Gather gather(std::move(bricks), c->load_staging, threads);
-  gather.release(std::min(n, 2));
+  Gather gather(std::move(bricks), c->load_staging, buffers, threads);
+  gather.release(std::min(n, buffers));
   for (int b = 0; b < n; ++b) {
     gather.wait(b);
     const BcLoadSrc& s = from[b];
     const size_t bytes = (size_t)(s.strides[2] * (std::min<int64_t>(c->bricks[b].hi[2] + 1, d.global_dims[2]) - s.origin[2]) * eb);
-    HIPCHECK(c, hipMemcpyAsync(c->dev[3], c->load_staging[b & 1], bytes, hipMemcpyHostToDevice, st));
-    HIPCHECK(c, hipEventRecord(c->load_copied[b & 1], st));
+    HIPCHECK(c, hipMemcpyAsync(c->dev[3], c->load_staging[b % buffers], bytes, hipMemcpyHostToDevice, st));
+    HIPCHECK(c, hipEventRecord(c->load_copied[b % buffers], st));
     HIPCHECK(c, convert(s, b, 1));
-    // the buffer of the brick after next
-    if (b + 2 < n) {
-      HIPCHECK(c, hipEventSynchronize(c->load_copied[b & 1]));
-      gather.release(b + 3);
+    // the buffer's next brick
+    if (b + buffers < n) {
+      HIPCHECK(c, hipEventSynchronize(c->load_copied[b % buffers]));
+      gather.release(b + buffers + 1);
     }
   }
   return BC_OK;
