@@ -14,7 +14,6 @@
 #include <map>
 #include <mutex>
 #include <string>
-#include <thread>
 #include <vector>
 
 #include "../../include/brickcast.h"
@@ -592,10 +591,7 @@ int load_from_host(bc_ctx* c, const void* src, const int64_t* strides, const int
     if (i == 0) HIPCHECK(c, e);
     break;
   }
-  // (a thread to start costs about what it copies of 256 KB)
-  const int threads = all < (int64_t(2) << 20) ? 0
-                      : (int)std::min<int64_t>({8, all >> 20, std::max<int64_t>(std::thread::hardware_concurrency(), 1)});
-  Gather gather(std::move(bricks), c->load_staging, buffers, threads);
+  Gather gather(std::move(bricks), c->load_staging, buffers, gather_threads(all));
   gather.release(std::min(n, buffers));
   for (int b = 0; b < n; ++b) {
     gather.wait(b);

@@ -1,8 +1,10 @@
 // Host side of a load from host memory: gathers the bricks of a strided source
 // into staging buffers, on threads of its own.
 #pragma once
+#include <sched.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 #include <condition_variable>
 #include <cstring>
@@ -10,6 +12,17 @@
 #include <thread>
 #include <utility>
 #include <vector>
+
+// threads for a source of so many bytes: none below 2 MiB (a thread to start
+// costs about what it copies of 256 KB), no more than a MiB each keeps busy, and
+// no more than the cores this process may run on
+inline int gather_threads(int64_t bytes) {
+  if (bytes < (int64_t(2) << 20)) return 0;
+  cpu_set_t cores;
+  const int usable = sched_getaffinity(0, sizeof cores, &cores) == 0 ? CPU_COUNT(&cores)
+                                                                      : (int)std::thread::hardware_concurrency();
+  return (int)std::min<int64_t>({8, bytes >> 20, std::max(usable, 1)});
+}
 
 // Threads that gather a host source's bricks into the staging buffers, each
 // brick in `kParts` runs of rows.  Brick b goes to buffer b % n_buffers and is

@@ -16,6 +16,10 @@ MAIN = r"""
 #include "bc_gather.h"
 
 int main(int argc, char** argv) {
+  if (argc == 2) {
+    printf("%d\n", gather_threads(atoll(argv[1])));
+    return 0;
+  }
   const int n = atoi(argv[1]), n_buffers = atoi(argv[2]), threads = atoi(argv[3]), stride = atoi(argv[4]);
   const int nx = 23, ny = 17, nz = 3 * n;   // bricks of nx - b % 3, ny, 3 voxels, 4 bytes each
   std::vector<uint32_t> src((size_t)nx * stride * (ny + 1) * nz);
@@ -78,3 +82,15 @@ def test_bricks_are_whole(program, n, buffers, threads, stride):
         r = subprocess.run([program] + [str(v) for v in (n, buffers, threads, stride)] + more, capture_output=True,
                            text=True, timeout=60)
         assert r.returncode == 0 and r.stdout.strip() == "0", r.stderr
+
+
+def test_threads_follow_the_cores_the_process_may_use(program):
+    def threads(size, cores=None):
+        set_cores = None if cores is None else (lambda: os.sched_setaffinity(0, cores))
+        return int(subprocess.run([program, str(size)], capture_output=True, text=True, timeout=60, check=True,
+                                  preexec_fn=set_cores).stdout)
+    mine = sorted(os.sched_getaffinity(0))
+    assert threads(1 << 20) == 0
+    for n in {1, min(3, len(mine)), len(mine)}:
+        assert threads(1 << 30, set(mine[:n])) == min(8, n)
+        assert threads(2 << 20, set(mine[:n])) == min(2, n)
