@@ -911,7 +911,11 @@ int bc_load_bricks(bc_ctx* c, const void* src, const int64_t strides[3], int src
     } catch (const std::exception& e) {   // (no host memory for the list of bricks)
       r = fail(c, BC_E_NOMEM, "bc_load_bricks: %s", e.what());
     }
-    if (r) return r;
+    if (r) {
+      // (copies on their way read the staging buffers, which the next load fills)
+      (void)hipStreamSynchronize(st);
+      return r;
+    }
   }
   HIPCHECK(c, hipStreamSynchronize(st));
   HIPCHECK(c, hipMemcpy(c->bricks.data(), dbricks, sizeof(BcBrick) * c->n_bricks, hipMemcpyDeviceToHost));
