@@ -1757,6 +1757,8 @@ int bc_cnn_gradients(bc_ctx* c, const float* coarse, const float* target, int n,
   if (!c) return BC_E_ARG;
   c->err.clear();
   if (!coarse || !target) return fail(c, BC_E_ARG, "bc_cnn_gradients: null image");
+  if ((reinterpret_cast<uintptr_t>(coarse) | reinterpret_cast<uintptr_t>(target)) & 15)
+    return fail(c, BC_E_ARG, "bc_cnn_gradients: images must be 16-byte aligned");
   int r = cnn_check_images(c, "bc_cnn_gradients", n, h, w);
   if (r) return r;
   HIPCHECK(c, hipSetDevice(c->device));
@@ -1775,6 +1777,8 @@ int bc_cnn_train_step(bc_ctx* c, const float* coarse, const float* target, int n
   if (!c) return BC_E_ARG;
   c->err.clear();
   if (!coarse || !target) return fail(c, BC_E_ARG, "bc_cnn_train_step: null image");
+  if ((reinterpret_cast<uintptr_t>(coarse) | reinterpret_cast<uintptr_t>(target)) & 15)
+    return fail(c, BC_E_ARG, "bc_cnn_train_step: images must be 16-byte aligned");
   if (!(lr > 0.0f) || !std::isfinite(lr)) return fail(c, BC_E_ARG, "bc_cnn_train_step: lr must be finite and > 0");
   int r = cnn_check_images(c, "bc_cnn_train_step", n, h, w);
   if (r) return r;
