@@ -52,8 +52,8 @@ struct BcFramePtrs {
   int64_t item_bound;     // ray caster with a workgroup per item: the bound on the items (0: persistent)
   int32_t storage;
   int32_t width, height;  // frame size (all views share it)
-  int32_t urgent;         // 1: the ray caster's waves issue at raised priority (2, and 3 while
-                          // evaluating); 0: at the base levels (0 and 1), for a pass that runs
+  int32_t urgent;         // persistent ray casting: 1: its waves issue at raised priority (2, and 3
+                          // while evaluating); 0: at the base levels (0 and 1), for a pass that runs
                           // beside a more urgent one
   int32_t tile_shift;     // screen tiles are (1 << tile_shift) x (64 >> tile_shift) pixels
   // the pass inputs in host-coherent pinned memory, which the set-up kernel
