@@ -1095,8 +1095,18 @@ int render_impl(bc_ctx* c, float* out, void* stream, float4* sub, int64_t sub_ca
   // the frame: the kernels of every pass (each pass's set-up kernel first
   // copies the pass inputs from the pinned slot)
   const bool captured = (c->use_graph || c->as_captured) && !no_alloc;
+  // A frame in the caller's own capture is launched again for the inputs that
+  // later frames leave in its slot: for more items than the views of now have.
+  // Its kernels take any number, here with enough workgroups to fill the chip.
+  bool recorded = captured;
+  if (!recorded && st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    HIPCHECK(c, hipStreamIsCapturing(st, &status));
+    recorded = status == hipStreamCaptureStatusActive;
+  }
   auto route = [&](BcFramePtrs& p, int64_t items, double step) {
-    p.item_bound = takes_quads(c, items, step, captured) ? std::min<int64_t>(std::max<int64_t>(items, 1), 1 << 20) : 0;
+    const int64_t least = recorded ? c->render_workgroups : 1;
+    p.item_bound = takes_quads(c, items, step, captured) ? std::min<int64_t>(std::max(items, least), 1 << 20) : 0;
   };
   auto enqueue = [&](hipStream_t s, hipEvent_t* e) -> int {
     if (e && c->timing_stages) HIPCHECK(c, hipEventRecord(e[0], s));
@@ -1104,7 +1114,7 @@ int render_impl(bc_ctx* c, float* out, void* stream, float4* sub, int64_t sub_ca
       route(f, c->view_tiles, dt);
       HIPCHECK(c, bc_launch_setup(f, s));
       if (e) HIPCHECK(c, hipEventRecord(e[1], s));
-      HIPCHECK(c, bc_launch_render(f, persistent_workgroups(c->view_tiles, c->render_workgroups, captured), s));
+      HIPCHECK(c, bc_launch_render(f, persistent_workgroups(c->view_tiles, c->render_workgroups, recorded), s));
       if (e) HIPCHECK(c, hipEventRecord(e[2], s));
       HIPCHECK(c, bc_launch_composite(f, reinterpret_cast<float4*>(out), s));
     } else {
