@@ -29,7 +29,6 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 // round to nearest, ties to even (one hardware conversion on gfx950)
 __device__ __forceinline__ uint16_t bf16_bits(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
-__device__ __forceinline__ float bf16_float(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
@@ -51,14 +50,14 @@ __device__ __forceinline__ int tap_offset(int tap) {
 }
 
 // element offsets (from the output pixel's input position) of the lane's
-// reduction indices at k-step ks: for CIN >= 8 one run of 8 channels of one
+// reduction indices at k-step ks: for CIN = 16 one run of 8 channels of one
 // tap, for CIN = 4 two taps of 4 channels; -1 for the zero padding past tap 8
 template <int CIN, int WIN, int SIN>
 __device__ __forceinline__ int2 lane_offsets(int g, int ks) {
-  if (CIN >= 8) {
-    // CIN = 32: tap = ks, channel 8 g; CIN = 16: tap = 2 ks + g/2, channel 8 (g%2)
-    const int o = tap_offset<CIN, WIN, SIN>(ks * (32 / CIN) + (8 * g) / CIN);
-    return make_int2(o < 0 ? -1 : o + (8 * g) % CIN, -1);
+  static_assert(CIN == 4 || CIN == 16, "tiles of 32 channels go through conv_hold");
+  if (CIN == 16) {
+    const int o = tap_offset<CIN, WIN, SIN>(2 * ks + g / 2);
+    return make_int2(o < 0 ? -1 : o + 8 * (g % 2), -1);
   }
   const int t0 = (ks * 32 + 8 * g) / 4;
   return make_int2(tap_offset<CIN, WIN, SIN>(t0), tap_offset<CIN, WIN, SIN>(t0 + 1));
@@ -72,7 +71,7 @@ __device__ __forceinline__ int swizzle(int c, int x) { return 8 * (c ^ ((x >> 2)
 
 template <int CIN>
 __device__ __forceinline__ bf16x8 load_a(const uint16_t* in, int pix, int2 off) {
-  if (CIN >= 8) {
+  if (CIN == 16) {
     if (off.x < 0) return as_bf16x8(make_uint4(0, 0, 0, 0));
     return as_bf16x8(*reinterpret_cast<const uint4*>(in + pix + off.x));
   }
@@ -375,8 +374,9 @@ __device__ void stage_tile(uint16_t* t, int sin, const float* __restrict__ img, 
 // mode 1: g = bf16(z * [mask > 0]) stored NHWC (backward-data with ReLU mask)
 // mode 2: last layer + loss: y = z + b, out = shuffle(y) + bilinear(x),
 //         g_y = bf16(2 (out - target) / count), squared error summed per tile
-template <int CIN, int COUT, int KS, int MODE>
+template <int CIN, int COUT, int MODE>
 __global__ __launch_bounds__(256, CIN == 32 ? 4 : 1) void layer_kernel(CnnLayerArgs a) {
+  constexpr int KS = (9 * CIN + 31) / 32;   // k-steps of 32 (tap, channel) pairs
   constexpr int SIN = CIN == 4 ? 4 : PSTRIDE;
   constexpr int NT = COUT / 16;
   __shared__ __attribute__((aligned(16))) uint16_t t[18 * 18 * SIN];
@@ -757,13 +757,13 @@ hipError_t cnn_launch_infer(const CnnInferArgs& a, int n, hipStream_t st) {
 
 hipError_t cnn_launch_layer(int layer, int mode, const CnnLayerArgs& a, int n, hipStream_t st) {
   dim3 grid((a.w + 15) / 16, (a.h + 15) / 16, n);
-  if (layer == 1 && mode == 0) layer_kernel<4, 32, 2, 0><<<grid, 256, 0, st>>>(a);
-  else if (layer == 2 && mode == 0) layer_kernel<32, 32, 9, 0><<<grid, 256, 0, st>>>(a);
-  else if (layer == 3 && mode == 2) layer_kernel<32, 16, 9, 2><<<grid, 256, 0, st>>>(a);
+  if (layer == 1 && mode == 0) layer_kernel<4, 32, 0><<<grid, 256, 0, st>>>(a);
+  else if (layer == 2 && mode == 0) layer_kernel<32, 32, 0><<<grid, 256, 0, st>>>(a);
+  else if (layer == 3 && mode == 2) layer_kernel<32, 16, 2><<<grid, 256, 0, st>>>(a);
   // backward-data of layer 3: input g_y (16 ch) -> g_a2 (32 ch) masked by a2
-  else if (layer == 3 && mode == 1) layer_kernel<16, 32, 5, 1><<<grid, 256, 0, st>>>(a);
+  else if (layer == 3 && mode == 1) layer_kernel<16, 32, 1><<<grid, 256, 0, st>>>(a);
   // backward-data of layer 2: input g_z2 (32 ch) -> g_a1 (32 ch) masked by a1
-  else if (layer == 2 && mode == 1) layer_kernel<32, 32, 9, 1><<<grid, 256, 0, st>>>(a);
+  else if (layer == 2 && mode == 1) layer_kernel<32, 32, 1><<<grid, 256, 0, st>>>(a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

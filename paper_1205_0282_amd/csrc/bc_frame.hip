@@ -43,7 +43,8 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 }
 
 // One wave: P*M and its Gauss-Jordan inverse with partial pivoting (a column
-// of the augmented matrix per lane, lanes 0-3 and 4-7), the eye, and the ray
+// of the augmented matrix per lane, lanes 0-3 and 4-7; never singular: the host
+// refuses such projections, and the modelview is rigid), the eye, and the ray
 // generator's vectors (an axis per lane).
 __device__ void view_params(SetupView& sv, BcViewParams& vp, int tile_shift, const int32_t* gdims) {
 #pragma clang fp contract(off)
@@ -62,7 +63,6 @@ __device__ void view_params(SetupView& sv, BcViewParams& vp, int tile_shift, con
     if (lane < 4) sv.pm[r * 4 + lane] = s;
     a[r] = col < 4 ? s : (r == col - 4 ? 1.0 : 0.0);
   }
-  bool singular = false;
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     double v[4];
@@ -83,7 +83,6 @@ __device__ void view_params(SetupView& sv, BcViewParams& vp, int tile_shift, con
       v[c] = sw ? vy : vx;
       v[r] = sw ? vx : vy;
     }
-    singular = singular || v[c] == 0.0;
     a[c] = a[c] / v[c];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -91,7 +90,6 @@ __device__ void view_params(SetupView& sv, BcViewParams& vp, int tile_shift, con
       a[r] = v[r] == 0.0 ? a[r] : a[r] - v[r] * a[c];
     }
   }
-  (void)singular;   // (the host refuses singular projections; the modelview is rigid)
   double Q[16];
 #pragma unroll
   for (int r = 0; r < 4; ++r)
