@@ -89,7 +89,7 @@ constexpr int kPasses = 3;   // learned frame: coarse, validation, conditional p
 constexpr double kQuadItems = 9.7e6;
 // Projection at one sample per voxel from FP32 and FP16: bricks' edge, rays'
 // spacing in voxels (takes_quads says when).
-constexpr double kQuadMipEdge = 192.0, kQuadMipSpacing = 1.75, kQuadMipF16 = 500.0;
+constexpr double kQuadMipEdge = 192.0, kQuadMipSpacing = 1.65, kQuadMipF16 = 500.0;
 
 }  // namespace
 
@@ -392,9 +392,9 @@ bool takes_quads(const bc_ctx* c, int64_t items, double step, bool captured) {
   // apart that they share few lines: the quads' better spread pays at any size,
   // from FP16 (whose lines hold twice the voxels) only for larger bricks or rays
   // further apart.  Render, quads / persistent, FP32 and FP16: 1024^3 in 205^3,
-  // spacing 1.79 0.88 and 0.99, 1.36 1.12 and 1.31; 1721x1721x1025 in 256^3,
-  // 2.03 0.87 and 0.93, 1.67 0.96 and 1.10, 1.27 1.08 and 1.25; in 192^3, 2.67
-  // 0.92 and 0.95, 2.14 0.97 and 1.06, 1.67 1.01 and 1.18.  FP8 bricks: 1.03 and more.
+  // spacing 1.70 0.91 and 1.03, 1.43 1.04 and 1.22; 1721x1721x1025 in 256^3, 2.03
+  // 0.87 and 0.93, 1.67 0.96 and 1.10, 1.58 1.03 and 1.20; in 192^3, 2.67 0.92 and
+  // 0.95, 2.14 0.97 and 1.06, 1.67 1.01 and 1.18.  FP8 bricks: 1.03 and more.
   if (c->op != BC_OP_MIP || !per_voxel || c->desc.storage == BC_FP8_E4M3 || edge < kQuadMipEdge) return false;
   const double spacing = ray_spacing(c);
   return spacing >= kQuadMipSpacing && (c->desc.storage == BC_F32 || spacing * edge >= kQuadMipF16);
