@@ -89,7 +89,8 @@ MEASURED_TRAFFIC = {
         "cube3000x3000x1500_f16_4views/f16/composite/fixed": 0.6563,
     },
 }
-KERNEL_SOURCES = ("bc_render.hip", "bc_types.h", "bc_kernels.h", "bc_ray.h", "bc_e4m3.h")
+# the ray caster's own, and the host's that decides which of its kernels a frame takes
+KERNEL_SOURCES = ("bc_render.hip", "bc_types.h", "bc_kernels.h", "bc_ray.h", "bc_e4m3.h", "bc_api.cpp")
 
 
 def kernel_sha256() -> str:
@@ -357,6 +358,25 @@ def timed_frames(bc, sets, out, steps, warmup):
     return elapsed / steps * 1e3, [m / n for m in stage_ms]
 
 
+def ray_casting_kernel(names) -> str | None:
+    """The ray-casting kernel among launched kernels' names (None without one)."""
+    found = [k for k in ("render_quad_kernel", "render_kernel") if any(k in n for n in names)]
+    return found[0] if len(found) == 1 else None
+
+
+def profiled_kernel(bc, out):
+    """The ray-casting kernel of a frame of the present views, from a profiled
+    (untimed) one; None under rocprofv3, which says it by itself."""
+    import torch
+    if any(k.startswith("ROCPROF") for k in os.environ):
+        return None
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as p:
+        bc.render(out)
+        torch.cuda.synchronize()
+    return ray_casting_kernel([e.key for e in p.key_averages()])
+
+
 def psnr_db(a, b) -> float:
     """PSNR (peak 1) of two device images over every pixel and channel."""
     mse = float(((a.double() - b.double()) ** 2).mean())
@@ -577,6 +597,8 @@ def main():
     bc.enable_timing(False)
     stage_ms = [side_ms[0] / n_side * n_timed, stage_ms[1], side_ms[2] / n_side * n_timed]
 
+    kernel = None if args.learned else profiled_kernel(bc, out)
+
     # the paper's statistic (untimed by the contract above): median of 10
     # frames per orbit angle, 75th percentile over the angles
     paper_stat = None
@@ -658,7 +680,7 @@ def main():
             "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
             "traffic": traffic,
-            "kernel": "render_kernel", "algo_bytes_per_launch": tot_bytes / args.steps,
+            "kernel": kernel, "algo_bytes_per_launch": tot_bytes / args.steps,
             # HBM bytes actually moved (counters), as a bandwidth and a fraction of peak
             "traffic_gbs": None if traffic is None else traffic / (render_s / args.steps) / 1e9,
             "traffic_frac": None if traffic is None else traffic / (render_s / args.steps) / 1e9 / HBM_PEAK_GBS,
