@@ -114,6 +114,7 @@ struct bc_ctx {
   size_t off_views_b = 0, off_order_b = 0, off_rects_b = 0, off_item_base_b = 0, off_item_perm_b = 0,
          off_item_entry_b = 0, off_ctr_b = 0;
   int max_occ_w[3] = {0, 0, 0};   // most occupancy words of a brick per axis
+  int64_t occ_words = 0;          // those of all bricks
   void* dev[4] = {nullptr, nullptr, nullptr, nullptr};
   // per-frame input ring (pinned host memory, kPasses pass inputs per slot) and events
   BcFrameIn* pinned[2] = {nullptr, nullptr};
@@ -789,6 +790,7 @@ int bc_plan(bc_ctx* c, const bc_volume_desc* d, int max_views, int max_w, int ma
                     : (int64_t)max_views * tiles_frame * std::min<int64_t>(nbt, 2 * ((int64_t)nb[0] + nb[1] + nb[2]) + 4);
   }
   c->max_tiles = max_tiles;
+  c->occ_words = occ_words;
   c->bytes[0] = align256((size_t)off * c->elem_bytes);
   size_t m = 0;
   c->off_bricks = m; m = align256(m + sizeof(BcBrick) * c->n_bricks);
@@ -1090,7 +1092,7 @@ int render_impl(bc_ctx* c, float* out, void* stream, float4* sub, int64_t sub_ca
   f.fin_bytes = (int32_t)fin_bytes;
   if (classify) {
     HIPCHECK(c, hipMemcpyAsync(meta + c->off_fin, pins, fin_bytes, hipMemcpyHostToDevice, st));
-    HIPCHECK(c, bc_launch_classify(f, c->max_occ_w, st));
+    HIPCHECK(c, bc_launch_classify(f, c->max_occ_w, c->occ_words, st));
   }
   // the frame: the kernels of every pass (each pass's set-up kernel first
   // copies the pass inputs from the pinned slot)

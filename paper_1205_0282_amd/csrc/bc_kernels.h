@@ -63,8 +63,8 @@ struct BcFramePtrs {
 };
 
 hipError_t bc_launch_setup(const BcFramePtrs& f, hipStream_t st);
-// max_w bounds the bricks' occupancy words per axis
-hipError_t bc_launch_classify(const BcFramePtrs& f, const int max_w[3], hipStream_t st);
+// max_w bounds the bricks' occupancy words per axis; `words` of them are used
+hipError_t bc_launch_classify(const BcFramePtrs& f, const int max_w[3], int64_t words, hipStream_t st);
 hipError_t bc_launch_render(const BcFramePtrs& f, int n_workgroups, hipStream_t st);
 hipError_t bc_launch_composite(const BcFramePtrs& f, float4* out, hipStream_t st);
 hipError_t bc_launch_psnr(const BcFramePtrs& f, const float4* ref, const float4* img, hipStream_t st);

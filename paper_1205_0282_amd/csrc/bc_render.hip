@@ -142,11 +142,13 @@ struct ClassifyArgs {
   int32_t y_tiles;        // 16-word tiles along y of the deepest brick
   int32_t z_words;        // words along z of one walk (even)
   int32_t z_chunks;       // walks along z of the tallest brick
+  uint32_t run;           // tiles dealt to an XCD at a time
+  int32_t max_words;      // words of the largest brick (a thread per word)
   int32_t mip;            // classify for maximum intensity projection
 };
 
 // one stored row: the 4 voxels of a micro-block row and the first one of the
-// next micro-block along x, as decoded values (FP8: the codes' values)
+// next micro-block along x, as decoded values
 template <int FMT>
 __device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t r, uint32_t ofs, float* v) {
   if (FMT == 0) {
@@ -167,14 +169,100 @@ __device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t r, uint32_t ofs,
     v[2] = decode<1>(p.y & 0xffffu, 1.f, 0.f);
     v[3] = decode<1>(p.y >> 16, 1.f, 0.f);
     v[4] = decode<1>(e, 1.f, 0.f);
-  } else {
-    const uint32_t p = __builtin_amdgcn_raw_buffer_load_b32(r, ofs, 0, 0);
-    const uint32_t e = __builtin_amdgcn_raw_buffer_load_b8(r, ofs + 4u, 0, 0);
-#pragma unroll
-    for (int x = 0; x < 4; ++x) v[x] = bc_e4m3_decode(p >> (8 * x));
-    v[4] = bc_e4m3_decode(e);
   }
 }
+
+// before[k] = the entry ahead of the first one at or after k that matters, by a
+// whole workgroup.  Those are the entries of non-zero opacity when compositing
+// (premultiplied colour is zero wherever opacity is), those different from the
+// first entry for maximum intensity projection.  Each thread takes a run of
+// entries; the first one that matters behind its run comes from a suffix scan.
+__device__ __forceinline__ void table_before(const ClassifyArgs& a, float* before, int32_t* wave_first) {
+  constexpr int kNone = 0x7fff;
+  const int K = a.fin->K, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float4* tab = reinterpret_cast<const float4*>(a.fin->table);
+  const float4 e0 = tab[0];
+  auto matters = [&](int k) -> bool {
+    const float4 e = tab[k];
+    if (!a.mip) return e.w != 0.0f;
+    return e.x != e0.x || e.y != e0.y || e.z != e0.z || e.w != e0.w;
+  };
+  const int per = (K + 255) / 256, k0 = min(K, tid * per), k1 = min(K, k0 + per);
+  int first = kNone;
+  for (int k = k1 - 1; k >= k0; --k)
+    if (matters(k)) first = k;
+  int run = first;   // smallest over this lane and those above it
+  for (int o = 1; o < 64; o <<= 1) {
+    const int other = __shfl_down(run, o);
+    if (lane + o < 64) run = min(run, other);
+  }
+  int behind = __shfl_down(run, 1);
+  if (lane == 63) behind = kNone;
+  if (lane == 0) wave_first[wave] = run;
+  __syncthreads();
+  for (int w = wave + 1; w < 4; ++w) behind = min(behind, wave_first[w]);
+  for (int k = k1 - 1; k >= k0; --k) {
+    if (matters(k)) behind = k;
+    before[k] = (float)(behind - 1);
+  }
+  __syncthreads();
+}
+
+// A brick's mapping of stored values to the table, and the cells that can reach
+// an entry that matters.
+//
+// FP8 compositing: the ray caster interpolates the codes' values and maps the
+// result to the table with the brick's scale and offset folded in, fma(q, scale
+// * s, fma(o, scale, bias)); the cells are bounded through the same mapping of
+// the same values, so that every index the ray caster can form lies inside the
+// checked range.  Projection compares decoded values: the decode is monotone, so
+// it is taken of the two bounds.
+template <int FMT>
+struct CellMap {
+  float csc, cbi, ds, dof, klast;
+  int il_mask;   // projection: every entry from the first one on
+  bool fold;
+  __device__ __forceinline__ CellMap(const ClassifyArgs& a, const BcBrick& br) {
+    const float sc = a.fin->tf_scale, bi = a.fin->tf_bias;
+    fold = FMT == 2 && !a.mip;
+    csc = fold ? sc * br.scale : sc;
+    cbi = fold ? __builtin_fmaf(br.offs, sc, bi) : bi;
+    ds = br.scale;
+    dof = br.offs;
+    klast = (float)(a.fin->K - 2);
+    il_mask = a.mip ? 0 : -1;
+  }
+  // bits of the four cells between two slices' rows, of which l and h are the
+  // smallest and largest of a row and its +y row at the 5 voxels along x
+  __device__ __forceinline__ uint32_t cells(const float* l0, const float* h0, const float* l1, const float* h1,
+                                            const float* before) const {
+    uint32_t bits = 0;
+    float l[5], h[5];
+#pragma unroll
+    for (int x = 0; x < 5; ++x) {
+      l[x] = fminf(l0[x], l1[x]);
+      h[x] = fmaxf(h0[x], h1[x]);
+    }
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      float lo = fminf(fminf(l[x], l[x + 1]), FLT_MAX), hi = fmaxf(fmaxf(h[x], h[x + 1]), -FLT_MAX);
+      if (FMT == 2 && !fold) {
+        lo = __builtin_fmaf(lo, ds, dof);
+        hi = __builtin_fmaf(hi, ds, dof);
+      }
+      // trilinear values lie within the corner range up to a few roundings
+      const float m = fmaxf(fabsf(lo), fabsf(hi)) * 9.5367431640625e-07f + 1e-30f;   // 2^-20
+      float xl = __builtin_fmaf(lo - m, csc, cbi), xh = __builtin_fmaf(hi + m, csc, cbi);
+      // entries [il, ih] with il = min(floor(xl), K - 2) and ih =
+      // min(floor(xh), K - 2) + 1: one of them matters if the first that
+      // does from il on, less one, is at most floor(xh)
+      xl = __builtin_amdgcn_fmed3f(xl, 0.0f, klast);
+      xh = __builtin_amdgcn_fmed3f(xh, 0.0f, klast);
+      bits |= before[(int)xl & il_mask] <= xh ? 1u << x : 0u;
+    }
+    return bits;
+  }
+};
 
 // Bound by the one read of the pool.  A stored row holds what the 4 cells of a
 // word's row need along x.  So a lane takes one row of cells and walks up z;
@@ -182,7 +270,7 @@ __device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t r, uint32_t ofs,
 // from the lane above it; a wave has 4 such columns along x, a workgroup four
 // waves along y, the last row of a wave taking its +y row from the next wave
 // through LDS and that of the last wave from memory.  A word's 32 bits meet by
-// two cross-lane ORs.  1024^3 FP32 cube (5.5 GB): 1.52 ms, 6.6 GB read, 4.3
+// two cross-lane ORs.  1024^3 FP32 cube (5.5 GB): 1.36 ms, 6.6 GB read, 4.9
 // TB/s; a thread per word with 75 loads of its own took 5.74 ms, and with
 // every lane loading its +y rows this form read 8.4 GB in 1.78 ms.
 template <int FMT>
@@ -190,55 +278,23 @@ __global__ __launch_bounds__(256) void classify_kernel(ClassifyArgs a) {
   __shared__ float before[BC_MAX_K];   // before[k] = the entry ahead of the first one at or after k that matters
   __shared__ int32_t wave_first[4];
   __shared__ __attribute__((aligned(16))) float edge[2][4][4][20];   // first rows: [turn parity][wave][column][slice][x]
-  constexpr int kNone = 0x7fff;
-  const int K = a.fin->K;
+  table_before(a, before, wave_first);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // the entries that matter: non-zero opacity when compositing (premultiplied
-  // colour is zero wherever opacity is), different from the first entry for
-  // maximum intensity projection.  Each thread takes a run of entries; the
-  // first one that matters behind its run comes from a suffix scan.
-  {
-    const float4* tab = reinterpret_cast<const float4*>(a.fin->table);
-    const float4 e0 = tab[0];
-    auto matters = [&](int k) -> bool {
-      const float4 e = tab[k];
-      if (!a.mip) return e.w != 0.0f;
-      return e.x != e0.x || e.y != e0.y || e.z != e0.z || e.w != e0.w;
-    };
-    const int per = (K + 255) / 256, k0 = min(K, tid * per), k1 = min(K, k0 + per);
-    int first = kNone;
-    for (int k = k1 - 1; k >= k0; --k)
-      if (matters(k)) first = k;
-    int run = first;   // smallest over this lane and those above it
-    for (int o = 1; o < 64; o <<= 1) {
-      const int other = __shfl_down(run, o);
-      if (lane + o < 64) run = min(run, other);
-    }
-    int behind = __shfl_down(run, 1);
-    if (lane == 63) behind = kNone;
-    if (lane == 0) wave_first[wave] = run;
-    __syncthreads();
-    for (int w = wave + 1; w < 4; ++w) behind = min(behind, wave_first[w]);
-    for (int k = k1 - 1; k >= k0; --k) {
-      if (matters(k)) behind = k;
-      before[k] = (float)(behind - 1);
-    }
-    __syncthreads();
-  }
-  const float sc = a.fin->tf_scale, bi = a.fin->tf_bias, klast = (float)(K - 2);
-  const int il_mask = a.mip ? 0 : -1;   // projection: every entry from the first one on
-  constexpr uint32_t esz = FMT == 0 ? 4 : (FMT == 1 ? 2 : 1);
+  static_assert(FMT < 2, "FP8: a thread per word");
+  constexpr uint32_t esz = FMT == 0 ? 4 : 2;
   const int cy = tid & 3;                                  // the lane's cell row in its word
   const bool top = (lane & 15) == 15, bottom = (lane & 15) == 0;   // the last and the first of its 16 rows
   int parity = 0;
-  // neighbouring tiles share rows: the tiles are dealt out in eight contiguous
-  // runs, one to the workgroups of each XCD (dispatched in turn), so that
+  // neighbouring tiles share rows: the tiles are dealt out in runs, to the
+  // workgroups of each XCD in turn (as these are dispatched), so that
   // neighbours meet in one L2
   const int per_plane = a.x_tiles * a.y_tiles;
-  const int64_t per_brick = (int64_t)per_plane * a.z_chunks, total = per_brick * a.n_bricks;
-  const int64_t run_len = (total + 7) / 8, run0 = (blockIdx.x & 7) * run_len, run1 = min(run0 + run_len, total);
-  for (int64_t item = run0 + (blockIdx.x >> 3); item < run1; item += gridDim.x >> 3) {
-    const int b = (int)(item / per_brick), rem = (int)(item - (int64_t)b * per_brick);
+  const uint32_t per_brick = (uint32_t)per_plane * a.z_chunks, total = per_brick * a.n_bricks;   // (65 * 17 * 129 * 4096 at most)
+  for (uint32_t at = blockIdx.x >> 3;; at += gridDim.x >> 3) {
+    const uint32_t round = at / a.run * 8 * a.run, item = round + (blockIdx.x & 7) * a.run + at % a.run;
+    if (round >= total) break;
+    if (item >= total) continue;
+    const int b = (int)(item / per_brick), rem = (int)(item - (uint32_t)b * per_brick);
     const int zc = rem / per_plane, tile = rem - zc * per_plane, ty = tile / a.x_tiles, tx = tile - ty * a.x_tiles;
     const BcBrick& br = a.bricks[b];
     const int WX = br.occ_w[0], WY = br.occ_w[1], WZ = br.occ_w[2];
@@ -257,15 +313,7 @@ __global__ __launch_bounds__(256) void classify_kernel(ClassifyArgs a) {
     // the lane's row in slice z (rows past the brick read as zero; their cells are masked)
     const uint32_t row0 = (((uint32_t)wy * mbx + (uint32_t)wx) * BC_MB_ELEMS + (uint32_t)cy * BC_ROW) * esz;
     const uint32_t dy = (mbx * BC_MB_ELEMS - 3u * BC_ROW) * esz;   // from a word's last row to the next word's first
-    // FP8 compositing: the ray caster interpolates the codes' values and maps
-    // the result to the table with the brick's scale and offset folded in,
-    // fma(q, scale * s, fma(o, scale, bias)); the cells are bounded through
-    // the same mapping of the same values, so that every index the ray caster
-    // can form lies inside the checked range.  Projection compares decoded
-    // values: the decode is monotone, so it is taken of the two bounds.
-    const bool fold = FMT == 2 && !a.mip;
-    const float csc = fold ? sc * br.scale : sc, cbi = fold ? __builtin_fmaf(br.offs, sc, bi) : bi;
-    const float ds = br.scale, dof = br.offs;
+    const CellMap<FMT> map(a, br);
     // N slices from z on: smallest and largest of the lane's row and its +y
     // row, at the 5 voxels along x
     auto slices = [&](int z, auto count, float (*lo)[5], float (*hi)[5]) {
@@ -303,31 +351,7 @@ __global__ __launch_bounds__(256) void classify_kernel(ClassifyArgs a) {
         }
     };
     auto cells = [&](const float* l0, const float* h0, const float* l1, const float* h1) -> uint32_t {
-      uint32_t bits = 0;
-      float l[5], h[5];
-#pragma unroll
-      for (int x = 0; x < 5; ++x) {
-        l[x] = fminf(l0[x], l1[x]);
-        h[x] = fmaxf(h0[x], h1[x]);
-      }
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        float lo = fminf(fminf(l[x], l[x + 1]), FLT_MAX), hi = fmaxf(fmaxf(h[x], h[x + 1]), -FLT_MAX);
-        if (FMT == 2 && !fold) {
-          lo = __builtin_fmaf(lo, ds, dof);
-          hi = __builtin_fmaf(hi, ds, dof);
-        }
-        // trilinear values lie within the corner range up to a few roundings
-        const float m = fmaxf(fabsf(lo), fabsf(hi)) * 9.5367431640625e-07f + 1e-30f;   // 2^-20
-        float xl = __builtin_fmaf(lo - m, csc, cbi), xh = __builtin_fmaf(hi + m, csc, cbi);
-        // entries [il, ih] with il = min(floor(xl), K - 2) and ih =
-        // min(floor(xh), K - 2) + 1: one of them matters if the first that
-        // does from il on, less one, is at most floor(xh)
-        xl = __builtin_amdgcn_fmed3f(xl, 0.0f, klast);
-        xh = __builtin_amdgcn_fmed3f(xh, 0.0f, klast);
-        bits |= before[(int)xl & il_mask] <= xh ? 1u << x : 0u;
-      }
-      return bits & row_mask;
+      return map.cells(l0, h0, l1, h1, before) & row_mask;
     };
     auto put = [&](int w, uint32_t bits) {
       bits <<= 4 * cy;
@@ -365,6 +389,68 @@ __global__ __launch_bounds__(256) void classify_kernel(ClassifyArgs a) {
         put(w1 - 1, half);
       }
     }
+  }
+}
+
+// FP8, and bricks so thin that few of those lanes would have a row: a thread per
+// word, with the word's 15 rows read through registers, three slices at a time
+// up y.  Bound by its loads, 15 rows of 64 lanes each; an FP8 row is one line's
+// part for several lanes, an FP32 one is not (1024^3 in 256^3 bricks: FP8 1.27
+// ms against 1.33 ms by rows; FP32 4.0 against 1.36).
+template <int FMT>
+__global__ __launch_bounds__(256) void classify_words_kernel(ClassifyArgs a) {
+  __shared__ float before[BC_MAX_K];
+  __shared__ int32_t wave_first[4];
+  table_before(a, before, wave_first);
+  constexpr uint32_t esz = FMT == 0 ? 4 : (FMT == 1 ? 2 : 1);
+  const int64_t total = (int64_t)a.n_bricks * a.max_words;
+  for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < total; g += (int64_t)gridDim.x * 256) {
+    const int b = (int)(g / a.max_words), w = (int)(g - (int64_t)b * a.max_words);
+    const BcBrick& br = a.bricks[b];
+    const int WX = br.occ_w[0], WY = br.occ_w[1];
+    if (w >= WX * WY * br.occ_w[2]) continue;
+    const int wx = w % WX, wy = w / WX % WY, wz = w / (WX * WY);
+    const int ncx = br.hi[0] - br.lo[0] + 1, ncy = br.hi[1] - br.lo[1] + 1, ncz = br.hi[2] - br.lo[2] + 1;
+    const uint32_t mask = (1u << clampi(ncx - wx * 4, 0, 4)) - 1u;
+    const uint32_t mbx = (uint32_t)br.mb[0], slab = mbx * (uint32_t)br.mb[1] * (BC_MB_ELEMS * esz);
+    // (the lanes' bricks differ: an address each, clamped to the last row and
+    // slice, whose copies belong to cells that are masked)
+    const char* pool = static_cast<const char*>(a.pool) + br.offset * esz;
+    const CellMap<FMT> map(a, br);
+    auto row = [&](int y, int z, float* v) {
+      y = min(y, ncy);
+      z = min(z, ncz);
+      const uint32_t ofs = (((uint32_t)(y >> 2) * mbx + (uint32_t)wx) * BC_MB_ELEMS + (uint32_t)(4 * (z & 3) + (y & 3)) * BC_ROW) * esz +
+                           (uint32_t)(z >> 2) * slab;
+#pragma unroll
+      for (int x = 0; x < 5; ++x) {
+        if (FMT == 0) v[x] = *reinterpret_cast<const float*>(pool + ofs + 4 * x);
+        else if (FMT == 1) v[x] = __half2float(*reinterpret_cast<const __half*>(pool + ofs + 2 * x));
+        else v[x] = bc_e4m3_decode(*reinterpret_cast<const uint8_t*>(pool + ofs + x));
+      }
+    };
+    uint32_t bits = 0;
+    float p[3][5];
+#pragma unroll
+    for (int z = 0; z < 3; ++z) row(4 * wy, 2 * wz + z, p[z]);
+#pragma unroll
+    for (int cy = 0; cy < 4; ++cy) {
+      float q[3][5], l[3][5], h[3][5];
+#pragma unroll
+      for (int z = 0; z < 3; ++z) {
+        row(4 * wy + cy + 1, 2 * wz + z, q[z]);
+#pragma unroll
+        for (int x = 0; x < 5; ++x) {
+          l[z][x] = fminf(p[z][x], q[z][x]);
+          h[z][x] = fmaxf(p[z][x], q[z][x]);
+          p[z][x] = q[z][x];
+        }
+      }
+      if (4 * wy + cy >= ncy) break;
+      bits |= (map.cells(l[0], h[0], l[1], h[1], before) & mask) << (4 * cy);
+      if (2 * wz + 1 < ncz) bits |= (map.cells(l[1], h[1], l[2], h[2], before) & mask) << (16 + 4 * cy);
+    }
+    a.occ[br.occ_offset + w] = bits;
   }
 }
 
@@ -1026,7 +1112,7 @@ hipError_t launch_render_fmt(const BcFramePtrs& f, int n_workgroups, hipStream_t
 
 }  // namespace
 
-hipError_t bc_launch_classify(const BcFramePtrs& f, const int max_w[3], hipStream_t st) {
+hipError_t bc_launch_classify(const BcFramePtrs& f, const int max_w[3], int64_t words, hipStream_t st) {
   ClassifyArgs a;
   a.bricks = f.bricks;
   a.fin = f.fin;
@@ -1042,12 +1128,38 @@ hipError_t bc_launch_classify(const BcFramePtrs& f, const int max_w[3], hipStrea
   a.z_words = 32;
   while (a.z_words > 4 && columns * ((max_w[2] + a.z_words - 1) / a.z_words) < 4096) a.z_words /= 2;
   a.z_chunks = (max_w[2] + a.z_words - 1) / a.z_words;
+  a.max_words = max_w[0] * max_w[1] * max_w[2];
   a.mip = f.op == 1;
+  // Each workgroup looks the table over for itself, 16 entries a thread at 4096:
+  // fewer of them on a long one (1024^3 FP32, 4096 entries: 1.85 ms with a
+  // workgroup per tile, 1.58 with 4096 of them; FP8 by words 1.39 with 8192,
+  // 1.35 with 1024; at 256 entries these grids cost 3 to 8 %).
+  const bool long_table = f.K > 1024;
+  const double rows = (double)max_w[0] * max_w[1] / (64.0 * a.x_tiles * a.y_tiles);   // of a walk's lanes, those with one
+  // By words: FP8 always (512^3, 256 entries, us by rows / by words: bricks of
+  // 64^3 346 / 175, of 512 x 8 x 512 626 / 229, of 8 x 512 x 512 290 / 240, of
+  // 600^3 in 12 x 300 x 300 326 / 354, the one shape where rows were ahead).
+  // The others where few lanes have a row: 1000 x 1 x 64 (a 16th) FP32 2192 / 899,
+  // FP16 2011 / 496; 512 x 8 x 512 (0.18) FP32 603 / 808, FP16 534 / 448; 300 x
+  // 12 x 300 (0.25) FP32 668 / 1174, FP16 608 / 661.
+  if (f.storage == 2 || rows < (f.storage == 0 ? 0.15 : 0.2)) {
+    const int64_t need = ((int64_t)f.n_bricks * a.max_words + 255) / 256;
+    const int grid = (int)std::min<int64_t>(need, long_table ? 1024 : 8192);
+    if (f.storage == 0) classify_words_kernel<0><<<grid, 256, 0, st>>>(a);
+    else if (f.storage == 1) classify_words_kernel<1><<<grid, 256, 0, st>>>(a);
+    else classify_words_kernel<2><<<grid, 256, 0, st>>>(a);
+    return hipGetLastError();
+  }
   const int64_t total = columns * a.z_chunks;
-  const int grid = (int)std::min<int64_t>((total + 7) / 8 * 8, 1 << 20);
+  a.run = (uint32_t)((total + 7) / 8);
+  // An eighth of the tiles to each XCD, unless the bricks' sizes differ: then most
+  // tiles of the small ones are empty, and they lie together (300 x 1000 x 1000 in
+  // 5 x 900 x 900, FP32: 2.50 ms in eighths, 0.93 in runs of 64; 1024^3 in 256^3:
+  // 1.36 in eighths, 1.45 in runs).
+  if ((double)words < 0.9 * f.n_bricks * a.max_words) a.run = (uint32_t)std::min<int64_t>(std::max<int64_t>(total / 64, 1), 64);
+  const int grid = (int)std::min<int64_t>((total + 8 * (int64_t)a.run - 1) / (8 * (int64_t)a.run) * (8 * (int64_t)a.run), long_table ? 4096 : 1 << 20);
   if (f.storage == 0) classify_kernel<0><<<grid, 256, 0, st>>>(a);
-  else if (f.storage == 1) classify_kernel<1><<<grid, 256, 0, st>>>(a);
-  else classify_kernel<2><<<grid, 256, 0, st>>>(a);
+  else classify_kernel<1><<<grid, 256, 0, st>>>(a);
   return hipGetLastError();
 }
 
