@@ -162,7 +162,8 @@ __host__ __device__ __forceinline__ int staged_row(int mb0) { return (4 * mb0 + 
 // encode + layout: brick first + blockIdx.x; a workgroup fills the row of
 // micro-blocks (all x) at micro-block coordinates (y, z) = blockIdx.y.  Its 16
 // source rows are read once, whole rows by whole waves, into LDS, and leave in
-// stored order as 16 bytes per thread; FP32 and FP16 storage, which need no
+// stored order as 16 bytes per thread (4 of FP8, whose conversion is the longer
+// part: 512^3 in bricks 62 wide 580 us with the min/max, 709 with 16); FP32 and FP16 storage, which need no
 // scale, take the brick's min/max on the way (one read of the source instead
 // of two).  Bound by that read and write: 1024^3 FP32
 // (4.3 GB in, 5.5 GB out) takes 1.95 ms, 5.0 TB/s; 1.60 ms of min/max and 3.20
@@ -171,8 +172,9 @@ template <typename T, int FMT>
 __global__ __launch_bounds__(256) void encode_kernel(SrcView s, const BcBrick* __restrict__ bricks, int first,
                                                      void* pool, BcCounters* ctr) {
   extern __shared__ float stage[];
-  constexpr int EPC = FMT == 0 ? 4 : (FMT == 1 ? 8 : 16);   // elements of a 16-byte chunk
-  constexpr int CPM = BC_MB_ELEMS / EPC;                    // chunks of a micro-block
+  constexpr int EPC = FMT == 1 ? 8 : 4;    // elements of a chunk: 16 bytes, or 4 of FP8
+  constexpr int CPM = BC_MB_ELEMS / EPC;   // chunks of a micro-block
+  constexpr int esz = FMT == 0 ? 4 : (FMT == 1 ? 2 : 1);
   static_assert(kEncodeThreads % CPM == 0, "a thread's place in a micro-block is fixed");
   const int b = first + (int)blockIdx.x;
   const BcBrick& br = bricks[b];
@@ -214,22 +216,22 @@ __global__ __launch_bounds__(256) void encode_kernel(SrcView s, const BcBrick* _
     }
     __syncthreads();
     if (tid < kEncodeThreads) {
-      u32x4* out = reinterpret_cast<u32x4*>(static_cast<char*>(pool) +
-                                            (br.offset + (int64_t)sl * mb0 * BC_MB_ELEMS) * (16 / EPC));
+      char* out = static_cast<char*>(pool) + (br.offset + (int64_t)sl * mb0 * BC_MB_ELEMS) * esz;
       for (int m = tid / CPM; m < mb0; m += kEncodeThreads / CPM) {
         const float* from = stage + 4 * m;
-        uint32_t w[4];
+        constexpr int W = EPC * esz / 4;
+        uint32_t w[W];
         if (FMT == 0) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) w[i] = __float_as_uint(from[at[i]]);
+          for (int i = 0; i < W; ++i) w[i] = __float_as_uint(from[at[i]]);
         } else if (FMT == 1) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
+          for (int i = 0; i < W; ++i)
             w[i] = __half_as_ushort(__float2half_rn(from[at[(2 * i) % EPC]])) |
                    (uint32_t)__half_as_ushort(__float2half_rn(from[at[(2 * i + 1) % EPC]])) << 16;
         } else {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
+          for (int i = 0; i < W; ++i) {
             w[i] = 0;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -239,12 +241,48 @@ __global__ __launch_bounds__(256) void encode_kernel(SrcView s, const BcBrick* _
           }
         }
         // (nothing reads them before the pool is whole: not kept in the caches)
-        __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, out + m * CPM + chunk);
+        char* to = out + (m * CPM + chunk) * (EPC * esz);
+        if constexpr (W == 4)
+          __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4*>(to));
+        else
+          __builtin_nontemporal_store(w[0], reinterpret_cast<uint32_t*>(to));
       }
     }
     __syncthreads();
   }
   if (FMT != 2) fold_minmax(mn, mx, ctr->minmax[b]);
+}
+
+// FP8 bricks narrow along x: the rows are too short for whole waves to read
+// them, so a thread takes four stored elements, anywhere in the brick, with a
+// load each.  Bound by the loads of partial lines and, in the load as a whole,
+// by the min/max that goes before.
+template <typename T>
+__global__ __launch_bounds__(256) void encode_narrow_kernel(SrcView s, const BcBrick* __restrict__ bricks, int first,
+                                                            void* pool) {
+  constexpr uint32_t UPM = BC_MB_ELEMS / 4;   // units of four elements of a micro-block
+  const BcBrick& br = bricks[first + (int)blockIdx.x];
+  const uint32_t mb0 = (uint32_t)br.mb[0], mb1 = (uint32_t)br.mb[1], units = mb0 * mb1 * (uint32_t)br.mb[2] * UPM;
+  const int cx = br.hi[0] - br.lo[0], cy = br.hi[1] - br.lo[1], cz = br.hi[2] - br.lo[2];
+  const float inv = 1.0f / br.scale, offs = br.offs;
+  for (uint32_t u = blockIdx.y * 256u + threadIdx.x; u < units; u += gridDim.y * 256u) {
+    const uint32_t mb = u / UPM, in = u - mb * UPM, sl = mb / mb0, mbx = mb - sl * mb0, mbz = sl / mb1, mby = sl - mbz * mb1;
+    T v[4];
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) {
+      const uint32_t e = 4 * in + j, row = e / BC_ROW, wx = e - row * BC_ROW;   // the fifth is the next micro-block's first voxel
+      // local ghosted index (0 <-> voxel lo-1); padding replicates the last ghost
+      const int lx = min((int)(mbx * 4 + wx), cx + 1), ly = min((int)(mby * 4 + (row & 3)), cy + 1),
+                lz = min((int)(mbz * 4 + (row >> 2)), cz + 1);
+      const int gx = min(max(br.lo[0] - 1 + lx, 0), s.nx - 1), gy = min(max(br.lo[1] - 1 + ly, 0), s.ny - 1),
+                gz = min(max(br.lo[2] - 1 + lz, 0), s.nz - 1);
+      v[j] = static_cast<const T*>(s.ptr)[(int64_t)(gx - s.ox) * s.sx + (int64_t)(gy - s.oy) * s.sy + (int64_t)(gz - s.oz) * s.sz];
+    }
+    uint32_t w = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w |= (uint32_t)bc_e4m3_encode((to_f32<T>(v[j]) - offs) * inv) << (8 * j);
+    __builtin_nontemporal_store(w, reinterpret_cast<uint32_t*>(static_cast<char*>(pool) + br.offset) + u);
+  }
 }
 
 inline SrcView make_src(const BcLoadSrc& s) {
@@ -304,6 +342,16 @@ hipError_t bc_launch_encode(const BcLoadSrc& src, const BcBrick* bricks, int fir
     kernel<<<grid, 256, lds, st>>>(s, bricks, first, pool, ctr);
     return hipGetLastError();
   };
+  // FP8 bricks up to 38 voxels wide by elements (512^3 in bricks of b x 512 x 512,
+  // min/max and encode, us staged / by elements: b = 1 22900 / 13200, 6 3910 /
+  // 2490, 14 1780 / 1260, 30 928 / 822, 38 761 / 726, 46 665 / 697, 62 582 / 607)
+  if (storage == 2 && max_mb0 <= 10) {
+    const int64_t units = max_rows * max_mb0 * (BC_MB_ELEMS / 4);
+    const dim3 flat((unsigned)count, (unsigned)std::max<int64_t>(1, std::min<int64_t>((units + 511) / 512, 65535)));
+    if (src.dtype == 0) encode_narrow_kernel<float><<<flat, 256, 0, st>>>(s, bricks, first, pool);
+    else encode_narrow_kernel<__half><<<flat, 256, 0, st>>>(s, bricks, first, pool);
+    return hipGetLastError();
+  }
   if (src.dtype == 0) {
     if (storage == 0) return launch(encode_kernel<float, 0>);
     if (storage == 1) return launch(encode_kernel<float, 1>);
