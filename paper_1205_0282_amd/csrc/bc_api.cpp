@@ -544,7 +544,7 @@ int load_from_host(bc_ctx* c, const void* src, const int64_t* strides, const int
   const int64_t eb = (int64_t)c->src_elem_bytes;
   std::vector<Gather::Brick> bricks;
   std::vector<BcLoadSrc> from;
-  int64_t all = 0;
+  int64_t all = 0, largest = 0;
   for (const BcBrick& hb : c->bricks) {
     int64_t lo[3], n[3];
     for (int a = 0; a < 3; ++a) {
@@ -564,6 +564,7 @@ int load_from_host(bc_ctx* c, const void* src, const int64_t* strides, const int
     const int64_t need = n[0] * n[1] * n[2] * eb;
     if ((size_t)need > c->bytes[3]) return fail(c, BC_E_NOMEM, "bc_load_bricks: scratch region too small");
     all += need;
+    largest = std::max(largest, need);
     BcLoadSrc s;
     s.dtype = d.src_dtype == BC_F32 ? 0 : 1;
     s.ptr = c->dev[3];
@@ -592,7 +593,7 @@ int load_from_host(bc_ctx* c, const void* src, const int64_t* strides, const int
     if (i == 0) HIPCHECK(c, e);
     break;
   }
-  Gather gather(std::move(bricks), c->load_staging, buffers, gather_threads(all));
+  Gather gather(std::move(bricks), c->load_staging, buffers, gather_threads(all, largest));
   gather.release(std::min(n, buffers));
   for (int b = 0; b < n; ++b) {
     gather.wait(b);

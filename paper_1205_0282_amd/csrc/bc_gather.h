@@ -15,9 +15,13 @@
 
 // threads for a source of so many bytes: none below 2 MiB (a thread to start
 // costs about what it copies of 256 KB), no more than a MiB each keeps busy, and
-// no more than the cores this process may run on
-inline int gather_threads(int64_t bytes) {
-  if (bytes < (int64_t(2) << 20)) return 0;
+// no more than the cores this process may run on; none either for bricks (of so
+// many bytes at most) below 96 KiB, which cost less to copy than to hand over
+// (host loads in ms with none / with 8: 256^3 in bricks of 16^3, 23 KB each, 117
+// / 148; 384^3 of 24^3, 70 KB, 135 / 169; 512^3 of 32^3, 157 KB, 183 / 170; 512^3
+// of 48^3, 500 KB, 85 / 63)
+inline int gather_threads(int64_t bytes, int64_t brick = INT64_MAX) {
+  if (bytes < (int64_t(2) << 20) || brick < (int64_t(96) << 10)) return 0;
   cpu_set_t cores;
   const int usable = sched_getaffinity(0, sizeof cores, &cores) == 0 ? CPU_COUNT(&cores)
                                                                       : (int)std::thread::hardware_concurrency();
