@@ -270,7 +270,7 @@ struct CellMap {
 // from the lane above it; a wave has 4 such columns along x, a workgroup four
 // waves along y, the last row of a wave taking its +y row from the next wave
 // through LDS and that of the last wave from memory.  A word's 32 bits meet by
-// two cross-lane ORs.  1024^3 FP32 cube (5.5 GB): 1.36 ms, 6.6 GB read, 4.9
+// two cross-lane ORs.  1024^3 FP32 cube (5.5 GB): 1.52 ms, 6.6 GB read, 4.3
 // TB/s; a thread per word with 75 loads of its own took 5.74 ms, and with
 // every lane loading its +y rows this form read 8.4 GB in 1.78 ms.
 template <int FMT>
@@ -395,8 +395,8 @@ __global__ __launch_bounds__(256) void classify_kernel(ClassifyArgs a) {
 // FP8, and bricks so thin that few of those lanes would have a row: a thread per
 // word, with the word's 15 rows read through registers, three slices at a time
 // up y.  Bound by its loads, 15 rows of 64 lanes each; an FP8 row is one line's
-// part for several lanes, an FP32 one is not (1024^3 in 256^3 bricks: FP8 1.27
-// ms against 1.33 ms by rows; FP32 4.0 against 1.36).
+// part for several lanes, an FP32 one is not (1024^3 in 256^3 bricks: FP8 1.43
+// ms against 1.51 by rows; FP32 2.6 times as long as by rows).
 template <int FMT>
 __global__ __launch_bounds__(256) void classify_words_kernel(ClassifyArgs a) {
   __shared__ float before[BC_MAX_K];
@@ -1131,12 +1131,14 @@ hipError_t bc_launch_classify(const BcFramePtrs& f, const int max_w[3], int64_t 
   a.max_words = max_w[0] * max_w[1] * max_w[2];
   a.mip = f.op == 1;
   // Each workgroup looks the table over for itself, 16 entries a thread at 4096:
-  // fewer of them on a long one (1024^3 FP32, 4096 entries: 1.85 ms with a
-  // workgroup per tile, 1.58 with 4096 of them; FP8 by words 1.39 with 8192,
-  // 1.35 with 1024; at 256 entries these grids cost 3 to 8 %).
+  // fewer of them on a long one (1024^3 FP32, 4096 entries: 2.10 ms with a
+  // workgroup per tile, 1.80 with 4096 of them; FP8 by words 3 % less with 1024
+  // than with 8192, 512^3 in bricks of 64^3 36 %; at 256 entries these grids cost
+  // 3 to 8 %).
   const bool long_table = f.K > 1024;
   const double rows = (double)max_w[0] * max_w[1] / (64.0 * a.x_tiles * a.y_tiles);   // of a walk's lanes, those with one
-  // By words: FP8 always (512^3, 256 entries, us by rows / by words: bricks of
+  // By words: FP8 always (512^3, 256 entries, us that a change of the transfer
+  // function adds to a frame, by rows / by words: bricks of
   // 64^3 346 / 175, of 512 x 8 x 512 626 / 229, of 8 x 512 x 512 290 / 240, of
   // 600^3 in 12 x 300 x 300 326 / 354, the one shape where rows were ahead).
   // The others where few lanes have a row: 1000 x 1 x 64 (a 16th) FP32 2192 / 899,
@@ -1154,8 +1156,8 @@ hipError_t bc_launch_classify(const BcFramePtrs& f, const int max_w[3], int64_t 
   a.run = (uint32_t)((total + 7) / 8);
   // An eighth of the tiles to each XCD, unless the bricks' sizes differ: then most
   // tiles of the small ones are empty, and they lie together (300 x 1000 x 1000 in
-  // 5 x 900 x 900, FP32: 2.50 ms in eighths, 0.93 in runs of 64; 1024^3 in 256^3:
-  // 1.36 in eighths, 1.45 in runs).
+  // 5 x 900 x 900, FP32, the same measure: 2.50 ms in eighths, 0.93 in runs of
+  // 64; 1024^3 in 256^3 4 % the other way).
   if ((double)words < 0.9 * f.n_bricks * a.max_words) a.run = (uint32_t)std::min<int64_t>(std::max<int64_t>(total / 64, 1), 64);
   const int grid = (int)std::min<int64_t>((total + 8 * (int64_t)a.run - 1) / (8 * (int64_t)a.run) * (8 * (int64_t)a.run), long_table ? 4096 : 1 << 20);
   if (f.storage == 0) classify_kernel<0><<<grid, 256, 0, st>>>(a);
