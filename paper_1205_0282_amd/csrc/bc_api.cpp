@@ -89,7 +89,7 @@ constexpr int kPasses = 3;   // learned frame: coarse, validation, conditional p
 constexpr double kQuadItems = 9.7e6;
 // Projection at one sample per voxel from FP32 and FP16: bricks' edge, rays'
 // spacing in voxels (takes_quads says when).
-constexpr double kQuadMipEdge = 192.0, kQuadMipSpacing = 1.65, kQuadMipF16 = 500.0;
+constexpr double kQuadMipEdge = 192.0, kQuadMipSpacing = 1.62, kQuadMipF16 = 465.0;
 
 }  // namespace
 
@@ -396,6 +396,10 @@ bool takes_quads(const bc_ctx* c, int64_t items, double step, bool captured) {
   // spacing 1.70 0.91 and 1.03, 1.43 1.04 and 1.22; 1721x1721x1025 in 256^3, 2.03
   // 0.87 and 0.93, 1.67 0.96 and 1.10, 1.58 1.03 and 1.20; in 192^3, 2.67 0.92 and
   // 0.95, 2.14 0.97 and 1.06, 1.67 1.01 and 1.18.  FP8 bricks: 1.03 and more.
+  // Those cubes are noise, of which the table shows the tail, and sources; the
+  // line moves with what is shown, which the host does not know.  Whole frames,
+  // spacing 1.56: 1024^3 with sources 0.98 and 1.17, most cells shown 0.68 and
+  // 0.83; 1721x1721x1025 of noise alone, 1.61: 1.34 and 1.6.
   if (c->op != BC_OP_MIP || !per_voxel || c->desc.storage == BC_FP8_E4M3 || edge < kQuadMipEdge) return false;
   const double spacing = ray_spacing(c);
   return spacing >= kQuadMipSpacing && (c->desc.storage == BC_F32 || spacing * edge >= kQuadMipF16);
