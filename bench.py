@@ -72,21 +72,21 @@ ORBIT = 64
 # [options]` (the 64-frame orbit, twice).  Valid only for the kernel sources
 # whose SHA-256 is recorded; any other source reports null.
 MEASURED_TRAFFIC = {
-    "sources_sha256": "186e74ebcdf2de510af7c702642bb1621564a3383ef66b400eb0285b88a568dd",
+    "sources_sha256": "e203cd77829017c013741f6c9d755d9181cf9e10ec9b323f0d3674ec59f5657f",
     "bytes": {   # "workload/storage/operator/step policy" -> bytes per launch
-        "cube1024_persp1920x1080/f32/composite/fixed": 2391245004,
-        "cube1024_persp1920x1080/f16/composite/fixed": 1537994514,
-        "cube1024_persp1920x1080/fp8/composite/fixed": 1035311169,
-        "cube1024_persp1920x1080/f32/mip/voxel": 3092028715,
-        "cube3000x3000x1500_f16_4views/f16/composite/fixed": 56615179447,
+        "cube1024_persp1920x1080/f32/composite/fixed": 2399865698,
+        "cube1024_persp1920x1080/f16/composite/fixed": 1547099869,
+        "cube1024_persp1920x1080/fp8/composite/fixed": 1040161313,
+        "cube1024_persp1920x1080/f32/mip/voxel": 3110878894,
+        "cube3000x3000x1500_f16_4views/f16/composite/fixed": 57056145187,
     },
     # L2 (TCC) hit rate over the same launches: TCC_HIT / (TCC_HIT + TCC_MISS)
     "l2_hit_rate": {
-        "cube1024_persp1920x1080/f32/composite/fixed": 0.7614,
-        "cube1024_persp1920x1080/f16/composite/fixed": 0.8124,
-        "cube1024_persp1920x1080/fp8/composite/fixed": 0.8294,
-        "cube1024_persp1920x1080/f32/mip/voxel": 0.3904,
-        "cube3000x3000x1500_f16_4views/f16/composite/fixed": 0.6563,
+        "cube1024_persp1920x1080/f32/composite/fixed": 0.7620,
+        "cube1024_persp1920x1080/f16/composite/fixed": 0.8121,
+        "cube1024_persp1920x1080/fp8/composite/fixed": 0.8307,
+        "cube1024_persp1920x1080/f32/mip/voxel": 0.4003,
+        "cube3000x3000x1500_f16_4views/f16/composite/fixed": 0.6540,
     },
 }
 # the ray caster's own, and the host's that decides which of its kernels a frame takes
