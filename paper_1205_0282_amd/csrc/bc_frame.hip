@@ -35,6 +35,11 @@ struct SetupView {
   int32_t persp, width, height, skip;
 };
 
+__device__ __forceinline__ void split(double v, float& hi, float& lo) {
+  hi = (float)v;
+  lo = (float)(v - (double)hi);
+}
+
 __device__ __forceinline__ double lane_value(double v, int lane) {
   const uint64_t u = (uint64_t)__double_as_longlong(v);
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
@@ -46,7 +51,7 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 // of the augmented matrix per lane, lanes 0-3 and 4-7; never singular: the host
 // refuses such projections, and the modelview is rigid), the eye, and the ray
 // generator's vectors (an axis per lane).
-__device__ void view_params(SetupView& sv, BcViewParams& vp, int tile_shift, const int32_t* gdims) {
+__device__ void view_params(SetupView& sv, BcViewParams& vp, int tile_shift) {
 #pragma clang fp contract(off)
   const int lane = threadIdx.x & 63, col = lane & 7;
   const double* mv = sv.in;
@@ -60,7 +65,10 @@ __device__ void view_params(SetupView& sv, BcViewParams& vp, int tile_shift, con
     double s = 0.0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) s = s + pr[k * 4 + r] * mv[(col & 3) * 4 + k];
-    if (lane < 4) sv.pm[r * 4 + lane] = s;
+    if (lane < 4) {
+      sv.pm[r * 4 + lane] = s;
+      vp.pm[r * 4 + lane] = s;
+    }
     a[r] = col < 4 ? s : (r == col - 4 ? 1.0 : 0.0);
   }
 #pragma unroll
@@ -105,11 +113,11 @@ __device__ void view_params(SetupView& sv, BcViewParams& vp, int tile_shift, con
     vp.tiles_x = (width + (1 << tile_shift) - 1) >> tile_shift;
     vp.tiles_y = (height + (64 >> tile_shift) - 1) >> (6 - tile_shift);
     vp.tau = (float)sv.tau;
-    vp.dt = step;
+    split(step, vp.dt_hi, vp.dt_lo);
   }
-  if (lane == 3) vp.idt = 1.0 / step;
-  if (lane == 4) vp.iw = 1.0 / (double)width;
-  if (lane == 5) vp.ih = 1.0 / (double)height;
+  if (lane == 3) split(1.0 / step, vp.idt_hi, vp.idt_lo);
+  if (lane == 4) split(1.0 / (double)width, vp.iw_hi, vp.iw_lo);
+  if (lane == 5) split(1.0 / (double)height, vp.ih_hi, vp.ih_lo);
   if (lane < 3) {
     const int x = lane;
     // eye e_a = -((R0a t0 + R1a t1) + R2a t2), without fused multiply-add
@@ -117,6 +125,8 @@ __device__ void view_params(SetupView& sv, BcViewParams& vp, int tile_shift, con
     const double dir = -mv[x * 4 + 2];
     sv.eye[x] = e;
     sv.dir[x] = dir;
+    vp.eye[x] = e;
+    vp.dir[x] = dir;
     const double q0 = x == 0 ? Q[0] : (x == 1 ? Q[4] : Q[8]), q1 = x == 0 ? Q[1] : (x == 1 ? Q[5] : Q[9]);
     const double q2 = x == 0 ? Q[2] : (x == 1 ? Q[6] : Q[10]), q3 = x == 0 ? Q[3] : (x == 1 ? Q[7] : Q[11]);
     double E, A, B, C;
@@ -139,11 +149,10 @@ __device__ void view_params(SetupView& sv, BcViewParams& vp, int tile_shift, con
       B = q1;
       C = q2 / n;
     }
-    vp.dims[x] = (double)gdims[x];
-    vp.e[x] = E;
-    vp.a[x] = A;
-    vp.b[x] = B;
-    vp.c[x] = C;
+    split(E, vp.e_hi[x], vp.e_lo[x]);
+    split(A, vp.a_hi[x], vp.a_lo[x]);
+    split(B, vp.b_hi[x], vp.b_lo[x]);
+    split(C, vp.c_hi[x], vp.c_lo[x]);
   }
 }
 
@@ -269,7 +278,7 @@ __device__ void setup_view(const BcFramePtrs& f, int v, bool copy, SetupView& sv
   }
   __syncthreads();
   if (sv.skip) return;
-  if (tid < 64) view_params(sv, f.views[v], f.tile_shift, f.gdims);
+  if (tid < 64) view_params(sv, f.views[v], f.tile_shift);
   __syncthreads();
   // (eight lanes to a brick: whole groups are in or out)
   for (int i = tid; i < 8 * nb; i += blockDim.x)

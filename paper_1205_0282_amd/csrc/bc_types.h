@@ -43,21 +43,29 @@ struct BcFrameIn {
   float table[BC_MAX_K][4];
 };
 
-// Derived per-view quantities written by the FP64 setup kernel and read by the
-// FP64 set-up of every ray.
+// Derived per-view quantities written by the FP64 setup kernel.  Vectors used
+// per ray are stored as double-float pairs (hi + lo) so that FP32 arithmetic
+// can place samples as accurately as FP64 would.
 struct BcViewParams {
   int32_t kind;              // 0 perspective, 1 orthographic
   int32_t width, height, tiles_x, tiles_y;
   int32_t tile_shift;        // log2 of the screen tile width: tiles are (1 << s) x (64 >> s) pixels
+  float dt_hi, dt_lo;        // step (double-float)
+  float idt_hi, idt_lo;      // 1 / step
+  float iw_hi, iw_lo;        // 1 / width
+  float ih_hi, ih_lo;        // 1 / height
   float tau;
-  int32_t pad_;
-  double dt, idt;            // step and its reciprocal
-  double iw, ih;             // 1 / width, 1 / height
-  double dims[3];            // the cube (here as FP64, so that no wave keeps converted copies)
+  float pad1;
   // perspective: e = eye, a/b/c: unnormalised direction u(x, y) = a x + b y + c
   // orthographic: e = origin at NDC (0, 0) on the near plane, a/b its NDC
   // derivatives, c = unit view direction
-  double e[3], a[3], b[3], c[3];
+  float e_hi[3], e_lo[3];
+  float a_hi[3], a_lo[3];
+  float b_hi[3], b_lo[3];
+  float c_hi[3], c_lo[3];
+  double eye[3];
+  double dir[3];
+  double pm[16];             // P*M, row-major
 };
 
 struct BcBrick {
