@@ -90,7 +90,7 @@ MEASURED_TRAFFIC = {
     },
 }
 # the ray caster's own, and the host's that decides which of its kernels a frame takes
-KERNEL_SOURCES = ("bc_render.hip", "bc_types.h", "bc_kernels.h", "bc_df.h", "bc_e4m3.h", "bc_api.cpp")
+KERNEL_SOURCES = ("bc_render.hip", "bc_types.h", "bc_kernels.h", "bc_df.h", "bc_ray.h", "bc_e4m3.h", "bc_api.cpp")
 
 
 def kernel_sha256() -> str:

@@ -398,8 +398,8 @@ bool takes_quads(const bc_ctx* c, int64_t items, double step, bool captured) {
   // 0.95, 2.14 0.97 and 1.06, 1.67 1.01 and 1.18.  FP8 bricks: 1.03 and more.
   // Those cubes are noise, of which the table shows the tail, and sources; the
   // line moves with what is shown, which the host does not know.  Whole frames,
-  // spacing 1.56: 1024^3 with sources 0.98 and 1.17, most cells shown 0.68 and
-  // 0.83; 1721x1721x1025 of noise alone, 1.61: 1.34 and 1.6.
+  // spacing 1.56: 1024^3 with sources 1.04 and 1.17 (1.87: FP16 0.96), most cells
+  // shown 0.68 and 0.83; 1721x1721x1025 of noise alone, 1.61: 1.34 and 1.6.
   if (c->op != BC_OP_MIP || !per_voxel || c->desc.storage == BC_FP8_E4M3 || edge < kQuadMipEdge) return false;
   const double spacing = ray_spacing(c);
   return spacing >= kQuadMipSpacing && (c->desc.storage == BC_F32 || spacing * edge >= kQuadMipF16);

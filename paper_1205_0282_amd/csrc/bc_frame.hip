@@ -10,6 +10,7 @@
 #include <float.h>
 #include "bc_types.h"
 #include "bc_kernels.h"
+#include "bc_ray.h"
 
 namespace {
 
@@ -31,6 +32,7 @@ struct SetupView {
   double in[32];       // modelview, projection (OpenGL order)
   double pm[16];       // P*M, row-major
   double eye[3], dir[3];
+  double e[3], a[3], b[3], c[3];   // ray generator: origin and its derivatives, direction of the centre
   double step, tau;
   int32_t persp, width, height, skip;
 };
@@ -65,10 +67,7 @@ __device__ void view_params(SetupView& sv, BcViewParams& vp, int tile_shift) {
     double s = 0.0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) s = s + pr[k * 4 + r] * mv[(col & 3) * 4 + k];
-    if (lane < 4) {
-      sv.pm[r * 4 + lane] = s;
-      vp.pm[r * 4 + lane] = s;
-    }
+    if (lane < 4) sv.pm[r * 4 + lane] = s;
     a[r] = col < 4 ? s : (r == col - 4 ? 1.0 : 0.0);
   }
 #pragma unroll
@@ -125,8 +124,6 @@ __device__ void view_params(SetupView& sv, BcViewParams& vp, int tile_shift) {
     const double dir = -mv[x * 4 + 2];
     sv.eye[x] = e;
     sv.dir[x] = dir;
-    vp.eye[x] = e;
-    vp.dir[x] = dir;
     const double q0 = x == 0 ? Q[0] : (x == 1 ? Q[4] : Q[8]), q1 = x == 0 ? Q[1] : (x == 1 ? Q[5] : Q[9]);
     const double q2 = x == 0 ? Q[2] : (x == 1 ? Q[6] : Q[10]), q3 = x == 0 ? Q[3] : (x == 1 ? Q[7] : Q[11]);
     double E, A, B, C;
@@ -149,10 +146,28 @@ __device__ void view_params(SetupView& sv, BcViewParams& vp, int tile_shift) {
       B = q1;
       C = q2 / n;
     }
-    split(E, vp.e_hi[x], vp.e_lo[x]);
     split(A, vp.a_hi[x], vp.a_lo[x]);
     split(B, vp.b_hi[x], vp.b_lo[x]);
     split(C, vp.c_hi[x], vp.c_lo[x]);
+    sv.e[x] = E;
+    sv.a[x] = A;
+    sv.b[x] = B;
+    sv.c[x] = C;
+  }
+}
+
+// where the rays start, an axis per lane
+__device__ void ray_origins(const SetupView& sv, BcViewParams& vp, const int32_t* gdims) {
+  const int x = threadIdx.x & 63;
+  if (x >= 3) return;
+  const double s = ray_shift(sv.e, sv.c, sv.persp ? sv.dir : sv.c, gdims);
+  const double by = sv.persp ? s : 1.0;
+  ray_moved(sv.e[x], s, sv.c[x], vp.e_hi[x], vp.e_lo[x]);
+  split(by * sv.a[x], vp.oa_hi[x], vp.oa_lo[x]);
+  split(by * sv.b[x], vp.ob_hi[x], vp.ob_lo[x]);
+  if (x == 0) {
+    vp.plane = !sv.persp || s != 0.0;
+    vp.t_min = s != 0.0 ? -INFINITY : 0.0f;
   }
 }
 
@@ -280,6 +295,7 @@ __device__ void setup_view(const BcFramePtrs& f, int v, bool copy, SetupView& sv
   if (sv.skip) return;
   if (tid < 64) view_params(sv, f.views[v], f.tile_shift);
   __syncthreads();
+  if (tid >= (int)blockDim.x - 64) ray_origins(sv, f.views[v], f.gdims);   // (beside the bricks, in the wave that they reach last)
   // (eight lanes to a brick: whole groups are in or out)
   for (int i = tid; i < 8 * nb; i += blockDim.x)
     brick_rect(sv, f.bricks[i >> 3], f.tile_shift, f.rects + ((int64_t)v * nb + (i >> 3)) * 4);

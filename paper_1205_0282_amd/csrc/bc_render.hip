@@ -18,7 +18,7 @@
 //            front-to-back compositing with early ray termination.
 //
 // Sample positions.  Per ray and brick the first sample's brick-local
-// position and the step vector are formed in double-float arithmetic and
+// position and the step vector are formed in double-float arithmetic (bc_ray.h) and
 // turned into 32.32 fixed point; every later sample position is an exact
 // integer sum, so the cell index and the interpolation weights of sample j
 // carry about 2^-32 voxels of error however far the ray has travelled.
@@ -46,7 +46,7 @@
 #include <type_traits>
 #include "bc_types.h"
 #include "bc_kernels.h"
-#include "bc_df.h"
+#include "bc_ray.h"
 #include "bc_e4m3.h"
 
 // Launch data that no wave writes while the ray caster runs (frame inputs,
@@ -452,106 +452,6 @@ __global__ __launch_bounds__(256) void classify_words_kernel(ClassifyArgs a) {
     }
     a.occ[br.occ_offset + w] = bits;
   }
-}
-
-// ------------------------------------------------------------------ rays
-__device__ __forceinline__ df dfv(float hi, float lo) { return df_make(hi, lo); }
-
-// smallest j >= 0 with t_in + (j + 1/2) dt >= t, that is ceil(q - 1/2) for
-// q = (t - t_in) / dt, taken exactly from the double-float q: q.hi - 1/2 is
-// exact (q stays below 2^22: the boundary refuses steps with more samples
-// along the cube's diagonal), and unless it is an integer the trailing part
-// (below half its ulp) cannot carry it past one
-__device__ __forceinline__ int first_index(df t_in, df idt, df t) {
-  const df q = df_mul(df_sub(t, t_in), idt);
-  const float c = q.hi - 0.5f;
-  const float j = ceilf(c);
-  return (int)fmaxf((j == c && q.lo > 0.0f) ? j + 1.0f : j, 0.0f);
-}
-
-// 32.32 fixed point of a double-float (each part truncated; error < 2^-31).
-// The leading part goes in two steps of 16 bits, each exact, so that no 64-bit
-// conversion (a dozen instructions) is needed; it stays below 2^15 for
-// positions in a brick and for every step that takes two samples in one.
-__device__ __forceinline__ int64_t q32(df a) {
-#pragma clang fp contract(off)
-  const float x = a.hi * 65536.0f, t = __builtin_truncf(x);
-  const int lo = (int)((x - t) * 65536.0f) + (int)(a.lo * 4294967296.0f);
-  return (int64_t)(int)t * 65536 + lo;
-}
-
-struct RaySeg {
-  int n;                 // samples of the ray inside the brick
-  int64_t u[3];          // first sample, ghosted brick-local coordinate minus 1/2, 32.32
-  int64_t s[3];          // step vector, 32.32
-};
-
-__device__ __forceinline__ df df_abs(df a) { return df_lt(a, df_from(0.0f)) ? df_neg(a) : a; }
-
-// Ray of pixel (px, py) against brick br: the samples t_j = t_in + (j+1/2) dt
-// of the ray's cube interval that fall in the brick's half-open box.  The step
-// is the view's, or with the per-voxel policy 1 / max_a |d_a| (consecutive
-// samples one voxel apart along the ray's dominant axis, the discrete ray
-// casting of Section 2.3.2).
-//
-// Of the cube only the entry is needed: the brick lies inside it, so a ray
-// that misses the cube misses the brick, one behind the eye ends the brick
-// before its first sample, and the brick's exit is never past the cube's (where
-// their faces coincide both come from the same arithmetic).  Every lane does
-// this once per brick its ray may cross, so it is kept short: about 700 vector
-// instructions where general double-float operations took 1900.
-__device__ bool ray_segment(KC(BcViewParams)& vp, const int32_t* gdims, KC(BcBrick)& br, int px, int py,
-                            bool per_voxel, RaySeg& seg) {
-  const int W = vp.width, H = vp.height;
-  const df x = df_mul_f(dfv(vp.iw_hi, vp.iw_lo), (float)(2 * px + 1 - W));
-  const df y = df_mul_f(dfv(vp.ih_hi, vp.ih_lo), (float)(H - 2 * py - 1));
-  df o[3], d[3];
-  if (vp.kind == 0) {
-    df u[3];
-    for (int a = 0; a < 3; ++a) {
-      o[a] = dfv(vp.e_hi[a], vp.e_lo[a]);
-      u[a] = df_fma2(dfv(vp.a_hi[a], vp.a_lo[a]), x, dfv(vp.b_hi[a], vp.b_lo[a]), y, dfv(vp.c_hi[a], vp.c_lo[a]));
-    }
-    const df ilen = df_rsqrt(df_norm2(u));
-    for (int a = 0; a < 3; ++a) d[a] = df_mul(u[a], ilen);
-  } else {
-    for (int a = 0; a < 3; ++a) {
-      o[a] = df_fma2(dfv(vp.a_hi[a], vp.a_lo[a]), x, dfv(vp.b_hi[a], vp.b_lo[a]), y, dfv(vp.e_hi[a], vp.e_lo[a]));
-      d[a] = dfv(vp.c_hi[a], vp.c_lo[a]);
-    }
-  }
-  // slab tests: entry into the cube, entry into and exit from the brick
-  df g0 = df_from(-INFINITY), b0 = g0, b1 = df_from(INFINITY);
-  bool miss = false;
-  for (int a = 0; a < 3; ++a) {
-    const float blo = (float)br.lo[a], bhi = (float)br.hi[a];
-    // (an axis along which the ray does not move: inside its slab or not at all)
-    const bool still = d[a].hi == 0.0f && d[a].lo == 0.0f;
-    miss = miss || (still && !(df_ge(o[a], df_from(blo)) && df_lt(o[a], df_from(bhi))));
-    const df id = df_rcp(df_make(still ? 1.0f : d[a].hi, d[a].lo));
-    const bool up = d[a].hi > 0.0f;
-    g0 = df_pick(still, g0, df_max(g0, df_plane(up ? 0.0f : (float)gdims[a], o[a], id)));
-    b0 = df_pick(still, b0, df_max(b0, df_plane(up ? blo : bhi, o[a], id)));
-    b1 = df_pick(still, b1, df_min(b1, df_plane(up ? bhi : blo, o[a], id)));
-  }
-  if (miss || !df_lt(b0, b1)) return false;
-  const df t_in = df_max(df_from(0.0f), g0);
-  df dt = dfv(vp.dt_hi, vp.dt_lo), idt = dfv(vp.idt_hi, vp.idt_lo);
-  if (per_voxel) {
-    idt = df_max(df_max(df_abs(d[0]), df_abs(d[1])), df_abs(d[2]));
-    dt = df_rcp(idt);
-  }
-  // (a ray has a direction: at least one axis took part)
-  const int j0 = first_index(t_in, idt, b0), j1 = first_index(t_in, idt, b1);
-  if (j1 <= j0) return false;
-  seg.n = j1 - j0;
-  const df t0 = df_add(t_in, df_mul_f(dt, (float)j0 + 0.5f));
-  for (int a = 0; a < 3; ++a) {
-    const df p = df_add(o[a], df_mul(t0, d[a]));
-    seg.u[a] = q32(df_add_f(p, 0.5f - (float)br.lo[a]));
-    seg.s[a] = q32(df_mul(dt, d[a]));
-  }
-  return true;
 }
 
 __device__ __forceinline__ int hi32(int64_t v) { return (int)(v >> 32); }

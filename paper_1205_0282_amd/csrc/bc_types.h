@@ -55,17 +55,18 @@ struct BcViewParams {
   float iw_hi, iw_lo;        // 1 / width
   float ih_hi, ih_lo;        // 1 / height
   float tau;
-  float pad1;
-  // perspective: e = eye, a/b/c: unnormalised direction u(x, y) = a x + b y + c
-  // orthographic: e = origin at NDC (0, 0) on the near plane, a/b its NDC
-  // derivatives, c = unit view direction
+  float t_min;               // where rays start from their origin: 0, or -infinity where it was moved
+  // perspective: a/b/c: unnormalised direction u(x, y) = a x + b y + c;
+  // orthographic: c = unit view direction.  A ray's origin is e, or with `plane`
+  // oa x + ob y + e (perspective: the eye, or a point of the plane that
+  // ray_shift() moves it to; orthographic: on the near plane, or moved too)
+  int32_t plane;
   float e_hi[3], e_lo[3];
+  float oa_hi[3], oa_lo[3];
+  float ob_hi[3], ob_lo[3];
   float a_hi[3], a_lo[3];
   float b_hi[3], b_lo[3];
   float c_hi[3], c_lo[3];
-  double eye[3];
-  double dir[3];
-  double pm[16];             // P*M, row-major
 };
 
 struct BcBrick {
