@@ -105,7 +105,6 @@ __device__ void view_params(SetupView& sv, BcViewParams& vp, int tile_shift) {
   const bool persp = pr[3] == 0.0 && pr[7] == 0.0 && pr[11] == -1.0 && pr[15] == 0.0;
   if (lane == 0) {
     sv.persp = persp;
-    vp.kind = persp ? 0 : 1;
     vp.width = width;
     vp.height = height;
     vp.tile_shift = tile_shift;
@@ -166,7 +165,7 @@ __device__ void ray_origins(const SetupView& sv, BcViewParams& vp, const int32_t
   split(by * sv.a[x], vp.oa_hi[x], vp.oa_lo[x]);
   split(by * sv.b[x], vp.ob_hi[x], vp.ob_lo[x]);
   if (x == 0) {
-    vp.plane = !sv.persp || s != 0.0;
+    vp.kind = !sv.persp ? 1 : (s != 0.0 ? 2 : 0);
     vp.t_min = s != 0.0 ? -INFINITY : 0.0f;
   }
 }

@@ -47,7 +47,7 @@ struct BcFrameIn {
 // per ray are stored as double-float pairs (hi + lo) so that FP32 arithmetic
 // can place samples as accurately as FP64 would.
 struct BcViewParams {
-  int32_t kind;              // 0 perspective, 1 orthographic
+  int32_t kind;              // 0 perspective, 1 orthographic, 2 perspective from a moved origin
   int32_t width, height, tiles_x, tiles_y;
   int32_t tile_shift;        // log2 of the screen tile width: tiles are (1 << s) x (64 >> s) pixels
   float dt_hi, dt_lo;        // step (double-float)
@@ -57,10 +57,10 @@ struct BcViewParams {
   float tau;
   float t_min;               // where rays start from their origin: 0, or -infinity where it was moved
   // perspective: a/b/c: unnormalised direction u(x, y) = a x + b y + c;
-  // orthographic: c = unit view direction.  A ray's origin is e, or with `plane`
-  // oa x + ob y + e (perspective: the eye, or a point of the plane that
-  // ray_shift() moves it to; orthographic: on the near plane, or moved too)
-  int32_t plane;
+  // orthographic: c = unit view direction.  A ray's origin is e (kind 0: the eye),
+  // or oa x + ob y + e: a point of the near plane, or of the plane that
+  // ray_shift() moves it to
+  int32_t pad1;
   float e_hi[3], e_lo[3];
   float oa_hi[3], oa_lo[3];
   float ob_hi[3], ob_lo[3];

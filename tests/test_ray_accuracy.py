@@ -70,7 +70,6 @@ int main(int argc, char** argv) {
     }
     // the view's record, as the set-up kernel writes it
     BcViewParams vp{};
-    vp.kind = kind;
     vp.width = W;
     vp.height = H;
     split(step, vp.dt_hi, vp.dt_lo);
@@ -79,7 +78,7 @@ int main(int argc, char** argv) {
     split(1.0 / H, vp.ih_hi, vp.ih_lo);
     const double s = ray_shift(E, c, c, dims);
     moved += s != 0.0;
-    vp.plane = kind || s != 0.0;
+    vp.kind = kind ? 1 : (s != 0.0 ? 2 : 0);
     vp.t_min = s != 0.0 ? -INFINITY : 0.0f;
     for (int a = 0; a < 3; ++a) {
       ray_moved(E[a], s, c[a], vp.e_hi[a], vp.e_lo[a]);
