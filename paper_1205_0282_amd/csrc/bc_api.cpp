@@ -78,15 +78,16 @@ constexpr int kPasses = 3;   // learned frame: coarse, validation, conditional p
 
 // Where the ray caster's two forms meet: kQuadItems is items times an item's
 // cost in four lanes to a ray, in samples (takes_quads has the cost).  Fitted to
-// 4137 frames (1 to 216 bricks of 12 to 900 voxels, FP32, FP16 and FP8, steps
-// 0.5 to 2, one view and four, close and far): of the 2877 it gives the quads,
-// two are more than 2% slower than the persistent launch (4% at most).  Render
-// us, persistent / quads, FP32 compositing on both sides of the line: 8 bricks
-// of 64^3, step 0.5, 28 K items 214 / 166; 64 of 64^3, step 0.5, 29 K 231 / 200
-// and 33 K 246 / 238; 64 of 64^3, step 2, 50 K 231 / 223 and 76 K 269 / 337; 64
-// of 128^3, step 1, 27 K 221 / 229 and 31 K 236 / 261; 64 of 250^3, step 0.5,
-// 9.3 K 362 / 290 and 20 K 526 / 629; one brick of 96^3, step 1, 130 K 1586 / 1017.
-constexpr double kQuadItems = 9.7e6;
+// 4104 frames (1 to 216 bricks of 12 to 256 voxels, FP32, FP16 and FP8, steps
+// 0.5 to 2, whole and magnified three times): the 3153 it gives the quads and the
+// 951 it does not take 0.2% longer than with the better of both throughout, 43
+// and 50 of them more than 2%, 18% and 25% at most.  Render us, persistent /
+// quads, FP32 compositing: 8 bricks of 64^3, step 1, 42 K items 273 / 287; of
+// 100^3, step 0.5, 26 K 271 / 270; 125 of 50^3, step 1, 39 K 185 / 208; step 0.5,
+// 26 K 181 / 171; 64 of 128^3, step 0.5, 14 K 209 / 203 and 19 K 245 / 274; 64 of
+// 250^3, step 0.5, 10 K 411 / 409 and 14 K 488 / 501; 64 of 64^3, step 2, 52 K
+// 212 / 292; one brick of 256^3, step 0.5, 11 K 311 / 245.
+constexpr double kQuadItems = 18e6;
 // Projection at one sample per voxel from FP32 and FP16: bricks' edge, rays'
 // spacing in voxels (takes_quads says when).
 constexpr double kQuadMipEdge = 192.0, kQuadMipSpacing = 1.62, kQuadMipF16 = 465.0;
@@ -380,15 +381,15 @@ bool takes_quads(const bc_ctx* c, int64_t items, double step, bool captured) {
     edge += (double)std::min<int64_t>(c->desc.brick_dims[a], c->desc.share_hi[a] - c->desc.share_lo[a]) / 3.0;
   const bool per_voxel = c->step_policy == BC_STEP_PER_VOXEL;
   const double ray = edge / (per_voxel ? 1.0 : step);
-  // An item's ray set-ups and idle lanes cost what 165 samples of its rays do;
-  // long rays cost more than their samples, as the persistent kernel's lanes
-  // find the last cell and word in registers where these gather them again.
-  // Few bricks leave queues empty (one for each brick, of eight), and the
-  // persistent launch pays 14 ns a claim of each queue: while rays are short that
-  // is what it takes.
+  // An item's ray set-ups (four times those of the persistent kernel) and idle
+  // lanes cost what 700 samples of its rays do; long rays cost more than their
+  // samples, as the persistent kernel's lanes find the last cell and word in
+  // registers where these gather them again.  Few bricks leave queues empty (one
+  // for each brick, of eight), and the persistent launch pays 14 ns a claim of
+  // each queue: while rays are short that is what it takes.
   const double queues = (double)std::min(c->n_bricks, 8);
-  const double claims = ray <= 200.0 ? std::max(770.0 / queues - 60.0 - 0.36 * ray, 0.0) : 0.0;
-  if ((double)items * (165.0 + ray + ray * ray / 1000.0 - claims) <= kQuadItems) return true;
+  const double claims = ray <= 250.0 ? std::max(3600.0 / queues - 150.0 - 0.2 * ray, 0.0) : 0.0;
+  if ((double)items * (700.0 + ray + ray * ray / 1000.0 - claims) <= kQuadItems) return true;
   // Projection at one sample per voxel through large bricks, with rays so far
   // apart that they share few lines: the quads' better spread pays at any size,
   // from FP16 (whose lines hold twice the voxels) only for larger bricks or rays
