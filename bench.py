@@ -72,21 +72,21 @@ ORBIT = 64
 # [options]` (the 64-frame orbit, twice).  Valid only for the kernel sources
 # whose SHA-256 is recorded; any other source reports null.
 MEASURED_TRAFFIC = {
-    "sources_sha256": "e203cd77829017c013741f6c9d755d9181cf9e10ec9b323f0d3674ec59f5657f",
+    "sources_sha256": "30ae6a615d8ca5e1341189ee10d26125bd4321a33e14397b0335ba0efd9b3035",
     "bytes": {   # "workload/storage/operator/step policy" -> bytes per launch
-        "cube1024_persp1920x1080/f32/composite/fixed": 2399865698,
-        "cube1024_persp1920x1080/f16/composite/fixed": 1547099869,
-        "cube1024_persp1920x1080/fp8/composite/fixed": 1040161313,
-        "cube1024_persp1920x1080/f32/mip/voxel": 3110878894,
-        "cube3000x3000x1500_f16_4views/f16/composite/fixed": 57056145187,
+        "cube1024_persp1920x1080/f32/composite/fixed": 2390575246,
+        "cube1024_persp1920x1080/f16/composite/fixed": 1540502714,
+        "cube1024_persp1920x1080/fp8/composite/fixed": 1035446236,
+        "cube1024_persp1920x1080/f32/mip/voxel": 3091566717,
+        "cube3000x3000x1500_f16_4views/f16/composite/fixed": 56662823527,
     },
     # L2 (TCC) hit rate over the same launches: TCC_HIT / (TCC_HIT + TCC_MISS)
     "l2_hit_rate": {
-        "cube1024_persp1920x1080/f32/composite/fixed": 0.7620,
-        "cube1024_persp1920x1080/f16/composite/fixed": 0.8121,
-        "cube1024_persp1920x1080/fp8/composite/fixed": 0.8307,
-        "cube1024_persp1920x1080/f32/mip/voxel": 0.4003,
-        "cube3000x3000x1500_f16_4views/f16/composite/fixed": 0.6540,
+        "cube1024_persp1920x1080/f32/composite/fixed": 0.7614,
+        "cube1024_persp1920x1080/f16/composite/fixed": 0.8109,
+        "cube1024_persp1920x1080/fp8/composite/fixed": 0.8293,
+        "cube1024_persp1920x1080/f32/mip/voxel": 0.3903,
+        "cube3000x3000x1500_f16_4views/f16/composite/fixed": 0.6557,
     },
 }
 # the ray caster's own, and the host's that decides which of its kernels a frame takes
